@@ -104,7 +104,7 @@ typedef struct {
                           E, A-DEF2 and the coarse start keep the FP32 AZ */
     int pt_range;      /* samples per work range of the P^T segmented reduction (a wave takes
                           the whole pixels starting in its range), a power of two in
-                          [256, 65536]; 0 = automatic: 2048, or with autotune the fastest of
+                          [256, 65536]; 0 = automatic: 512, or with autotune the fastest of
                           512 / 1024 / 2048 / 4096 timed on the plan's own data.  Results depend on
                           it at rounding level (the order of additions within a pixel) */
 } mm_opts;

@@ -1154,8 +1154,9 @@ constexpr int kAzGroup = 8;
 // P^T work range (samples per wave) of the A Z passes, whatever range the plan's P^T
 // takes: the eight-column pass holds few waves per SIMD (its registers), and shorter
 // ranges only add wave start-up work there (A Z build of the 2^24 raster with ranges of
-// 512 / 2048 / 4096 samples: plan 9.76 / 9.16 / 9.06 ms)
-constexpr int64_t kAzPtRange = 4096;
+// 512 / 2048 / 4096 samples: plan 9.76 / 9.16 / 9.06 ms).  A problem of fewer samples than
+// fill the chip's resident waves at that range (two per SIMD) takes shorter ones.
+constexpr int64_t kAzPtRange = 4096, kAzMinWaves = 2048;
 
 // dense row blocks of the batched Gram products, zd and azr together (bytes)
 constexpr int64_t kGramBudget = (int64_t)1 << 30;
@@ -1403,7 +1404,7 @@ int build_coarse(mm_plan_t pl) {
     // others write zeros without loading.
     const bool mixed = pl->opts.precision == MM_MIXED;
     const int64_t pt_keep = pl->pt_range;  // the plan's P^T range, restored after A Z
-    if (pt_keep != kAzPtRange) MM_TRY(build_wave_ranges(pl, kAzPtRange));
+    MM_TRY(build_wave_ranges(pl, kAzPtRange, kAzMinWaves));
     DBuf<double> azd;
     DBuf<float> azf;
     if (mixed) MM_TRY(azf.alloc((size_t)azd_off[B]));
@@ -1514,7 +1515,7 @@ int build_coarse(mm_plan_t pl) {
     tmp.release();
     todg.release();
     on.release();
-    if (pt_keep != kAzPtRange) MM_TRY(build_wave_ranges(pl, pt_keep));
+    MM_TRY(build_wave_ranges(pl, pt_keep));
     tick("AZ");
     // per problem: E_b = Z_b^T (AZ)_b on the matrix cores, independent subset, E_b^-1
     // every problem's E_b = Z_b^T (AZ)_b on the matrix cores into one device array

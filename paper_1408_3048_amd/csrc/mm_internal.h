@@ -231,7 +231,7 @@ struct mm_plan_s {
     std::vector<int64_t> h_samp, h_ooff;
     std::vector<int64_t> h_soff;        // [B+1] first padded sorted position of every problem
     std::vector<int64_t> h_pn;          // [B] samples of every problem
-    int64_t pt_range = 2048;            // samples per P^T work range
+    int64_t pt_range = 512;             // samples per P^T work range
     int64_t n_sorted = 0;               // padded sorted length (problems start 8-aligned)
     mm::DBuf<int32_t> int_prob;         // [n_int] problem of every interval
     mm::DBuf<int64_t> ooff;             // [B+1] compact pixel offsets
@@ -376,8 +376,16 @@ int toeplitz_tod64(mm_plan_t pl, const void* y, int y_f64, double* z);
 int toeplitz_tod32(mm_plan_t pl, const void* y, int y_f64, float* z);
 
 // ---- pointing.hip
-// P^T work ranges (wave_pix, wave_prob, wave_off) for per_wave samples per range
-int build_wave_ranges(mm_plan_t pl, int64_t per_wave);
+// Samples per P^T work range unless asked for or autotuned.  A range is one wave's serial
+// chain of 256-sample chunks, so long ranges leave a small problem on few waves: P^T in us at
+// ranges of 512 / 2048 samples, FP64: 2^14 samples 6.8 / 14.9, 2^18 (I) 6.4 / 10.7, 2^20
+// 10.3 / 22.3, 2^22 32.5 / 31.6, 2^24 105 / 109; FP32: 2^20 7.7 / 15.8, 2^22 15.9 / 18.8, 2^24
+// 54.8 / 57.3, 2^25 ring scan 159 / 164.
+constexpr int64_t kPtRange = 512;
+// P^T work ranges (wave_pix, wave_prob, wave_off) for per_wave samples per range; with
+// min_waves > 0 a problem whose samples make fewer ranges takes smaller ones (halved down to
+// kPtRange), a rule on the problem alone so that its sums do not depend on the batch
+int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves = 0);
 // the P^T range: opts.pt_range, else the fastest candidate (autotune) or the default
 int tune_pt_range(mm_plan_t pl);
 // x = P^T z for the problems in mask

@@ -268,10 +268,11 @@ __global__ void k_prob_minmax(const int32_t* __restrict__ pix, int64_t n,
 }
 
 // P^T work ranges: the sorted samples of problem b (from its padded start soff[b]) are cut
-// at soff[b] + k per_wave, each wave taking whole pixels; wave w belongs to problem wprob[w]
+// at soff[b] + k pw[b], each wave taking whole pixels; wave w belongs to problem wprob[w]
 __global__ void k_wave_ranges(const int64_t* __restrict__ seg, const int64_t* __restrict__ ooff,
                               const int64_t* __restrict__ soff, const int64_t* __restrict__ woff,
-                              int B, int64_t n_obs, int64_t n_waves, int64_t per_wave,
+                              const int64_t* __restrict__ pw, int B, int64_t n_obs,
+                              int64_t n_waves,
                               int32_t* __restrict__ wp, int32_t* __restrict__ wprob) {
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w <= n_waves;
          w += (int64_t)gridDim.x * blockDim.x) {
@@ -281,7 +282,7 @@ __global__ void k_wave_ranges(const int64_t* __restrict__ seg, const int64_t* __
         }
         const int b = find_range(woff, B, w);
         wprob[w] = b;
-        const int64_t target = soff[b] + (w - woff[b]) * per_wave;
+        const int64_t target = soff[b] + (w - woff[b]) * pw[b];
         int64_t lo = ooff[b], hi = ooff[b + 1];  // first c in [ooff[b], ooff[b+1]] with seg[c] >= target
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
@@ -574,7 +575,7 @@ int build_pointing(mm_plan_t pl, const int32_t* pix, const void* weights, int wd
     for (int b = 0; b < B; ++b) pl->h_pn[b] = s0[b + 1] - s0[b];
     MM_TRY(pl->soff.alloc(B + 1));
     MM_HIP(hipMemcpyAsync(pl->soff.p, pl->h_soff.data(), (B + 1) * 8, hipMemcpyHostToDevice, st));
-    MM_TRY(build_wave_ranges(pl, pl->opts.pt_range > 0 ? pl->opts.pt_range : 2048));
+    MM_TRY(build_wave_ranges(pl, pl->opts.pt_range > 0 ? pl->opts.pt_range : kPtRange));
     // weights, time-ordered and pixel-sorted
     if (pl->n_s == 3) {
         const bool mixed = pl->opts.precision == MM_MIXED;
@@ -601,20 +602,28 @@ int build_pointing(mm_plan_t pl, const int32_t* pix, const void* weights, int wd
 }
 
 // P^T work ranges: problem b's sorted samples (from its padded start) are cut every
-// per_wave samples; each range's wave takes the whole pixels that start in it
-int build_wave_ranges(mm_plan_t pl, int64_t per_wave) {
+// per_wave samples (or fewer, see min_waves); each range's wave takes the whole pixels that
+// start in it
+int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves) {
     hipStream_t st = pl->stream;
     const int B = pl->n_prob;
     std::vector<int64_t> woff(B + 1, 0);
-    for (int b = 0; b < B; ++b) woff[b + 1] = woff[b] + (pl->h_pn[b] + per_wave - 1) / per_wave;
+    std::vector<int64_t> pw(B, per_wave);
+    for (int b = 0; b < B; ++b) {
+        while (pw[b] > kPtRange && pl->h_pn[b] < min_waves * pw[b]) pw[b] /= 2;
+        woff[b + 1] = woff[b] + (pl->h_pn[b] + pw[b] - 1) / pw[b];
+    }
     pl->n_waves = woff[B];
     pl->pt_range = per_wave;
+    DBuf<int64_t> d_pw;
+    MM_TRY(d_pw.alloc(B));
+    MM_HIP(hipMemcpyAsync(d_pw.p, pw.data(), B * 8, hipMemcpyHostToDevice, st));
     MM_TRY(pl->wave_off.alloc(B + 1));
     MM_HIP(hipMemcpyAsync(pl->wave_off.p, woff.data(), (B + 1) * 8, hipMemcpyHostToDevice, st));
     MM_TRY(pl->wave_pix.alloc(pl->n_waves + 1));
     MM_TRY(pl->wave_prob.alloc(std::max<int64_t>(1, pl->n_waves)));
     hipLaunchKernelGGL(k_wave_ranges, dim3(grid_for(pl->n_waves + 1)), dim3(256), 0, st, pl->seg.p,
-                       pl->ooff.p, pl->soff.p, pl->wave_off.p, B, pl->n_obs, pl->n_waves, per_wave,
+                       pl->ooff.p, pl->soff.p, pl->wave_off.p, d_pw.p, B, pl->n_obs, pl->n_waves,
                        pl->wave_pix.p, pl->wave_prob.p);
     MM_HIP(hipGetLastError());
     return MM_OK;

@@ -1,0 +1,57 @@
+"""Rules that choose a kernel's split or variant by the sizes of a problem: results on either
+side of each line, against the oracle, against the general path or bit for bit where the
+library promises it."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+import synth  # noqa: E402
+from paper_1408_3048_amd import Plan  # noqa: E402
+
+
+def _gpu_plan(scans, **kw):
+    """One plan of the given scans, each an independent problem."""
+    pix, off, base = [], [np.zeros(1, np.int64)], 0
+    for sc in scans:
+        pix.append(sc.pix.astype(np.int64) + base)
+        off.append(off[-1][-1] + sc.offsets[1:])
+        base += sc.n_pix
+    w = np.concatenate([sc.weights for sc in scans])
+    psd = np.concatenate([np.stack([sc.sigma, sc.fknee, sc.alpha], 1) for sc in scans])
+    prob = np.cumsum([0] + [sc.n_intervals for sc in scans])
+    return Plan(torch.from_numpy(np.concatenate(pix).astype(np.int32)).cuda(),
+                torch.from_numpy(w).cuda(), base, np.concatenate(off), psd, n_stokes=3,
+                lam=scans[0].lam, f_samp=scans[0].f_samp, problem_intervals=prob, **kw)
+
+
+def test_pt_range_of_coarse_columns_depends_on_the_problem_alone():
+    """The P^T passes of the A Z build take ranges by the size of each problem: 512 samples for
+    2^17 samples, 1024 for 2,166,784 (just past 2048 ranges of 1024).  Each problem of a batch
+    equals its standalone plan bit for bit, and the mixed preconditioner is the FP64 plan's to
+    the bar of FP32 columns (it depends on their span alone)."""
+    kw = dict(n_det=4, lam=256, fknee_range=(2.0, 4.0), alpha_range=(1.0, 2.0))
+    scans = [synth.raster_iqu(side=64, spp=4, interval_len=2 ** 12, seed_key=71, **kw),
+             synth.raster_iqu(side=184, spp=8, interval_len=67712, seed_key=72, **kw)]
+    opts = dict(coarse=True, az_fp16=False, fft_len_f64=4096, fft_len_f32=4096)
+    pb = _gpu_plan(scans, precision="mixed", **opts)
+    assert pb.pt_range() == 512
+    off = pb.problem_pixels() * 3
+    r = torch.randn(pb.n_vec, dtype=torch.float64, device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(3))
+    zb = pb.precond_2lvl(r)
+    for b, sc in enumerate(scans):
+        p1 = Plan.from_scan(sc, precision="mixed", **opts)
+        z1 = p1.precond_2lvl(r[off[b]:off[b + 1]].contiguous())
+        assert torch.equal(z1, zb[off[b]:off[b + 1]]), b
+        p64 = Plan.from_scan(sc, precision="fp64", **opts)
+        z64 = p64.precond_2lvl(r[off[b]:off[b + 1]].contiguous())
+        assert float((z1 - z64).norm() / z64.norm()) < 1e-4, b  # A Z in FP32
+        p1.close()
+        p64.close()
+    pb.close()
