@@ -1166,6 +1166,7 @@ __global__ void k_gather_t0(const double* __restrict__ taps, const int64_t* __re
     if (g < nk) t0[g] = taps[toff[g]];
 }
 
+constexpr int64_t kCus = 256;  // compute units of the chip
 constexpr int kMaxLogM64 = 13, kMaxLogM32 = 14, kMinLogM = 10;
 
 int64_t count_tiles(const std::vector<int64_t>& off, int64_t lmax) {
@@ -1383,7 +1384,11 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
         // smallest modelled time: tiles x n_r x (log2 n_r + 4), doubled for a tile whose
         // LDS leaves room for only one resident tile per CU (160 KB): a second tile hides
         // the other's window load (measured: 32768-point FP32 tiles at lambda = 4096 take
-        // 1.27x the time of 16384-point ones, for 0.72x the modelled work)
+        // 1.27x the time of 16384-point ones, for 0.72x the modelled work).  Fewer tiles than
+        // CUs count as one tile per CU: such a launch takes the time of one tile, so the
+        // shorter length wins (A x of 2^18 intensity samples, lambda = 1024, FP64: 24.2 us
+        // with 128 tiles of 4096 points, 32.9 with 48 of 8192; 2^20 IQU samples, lambda = 2048,
+        // FP32: 32.0 us with 256 tiles of 8192, 34.9 with 96 of 16384)
         double best = 0.0;
         for (int l = kMinLogM; l <= maxlogm; ++l) {
             const int64_t nr = (int64_t)2 << l;
@@ -1391,8 +1396,8 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
             if (lmax < nr / 4) continue;
             const int64_t tile_lds = nr * (fp64 ? 8 : 4);
             const double resident = (160 * 1024) / tile_lds >= 2 ? 1.0 : 2.0;
-            const double cost =
-                (double)count_tiles(pl->h_off, lmax) * (double)nr * (l + 5) * resident;
+            const double tiles = (double)std::max<int64_t>(count_tiles(pl->h_off, lmax), kCus);
+            const double cost = tiles * (double)nr * (l + 5) * resident;
             if (logm == 0 || cost < best) {
                 best = cost;
                 logm = l;
