@@ -344,6 +344,9 @@ int host_taps(mm_plan_t pl);
 int kernel_taps(mm_plan_t pl, int what, std::vector<double>& taps, std::vector<int64_t>& toff,
                 std::vector<int64_t>& tcnt);
 
+// device table of exp(-2 pi i q / n), q < count, enqueued on the plan's stream
+int fft_twiddles(mm_plan_t pl, int64_t count, int64_t n, double* tw);
+
 // ---- adjoint.hip
 // c[j][k], k = 0..lambda (device, zero past K_j): lag cross-correlations of u and v per interval
 int lag_correlations(mm_plan_t pl, const double* u, const double* v, double* c);

@@ -55,3 +55,38 @@ def test_pt_range_of_coarse_columns_depends_on_the_problem_alone():
         p1.close()
         p64.close()
     pb.close()
+
+
+@pytest.mark.parametrize("lam,lens", [
+    (0, [700, 1]),
+    (64, [1, 2, 511, 512, 513, 2048, 2049, 300]),
+    (512, [1, 512, 513, 1024, 5000]),
+    (513, [1024, 1025, 4097, 40]),
+    (1024, [9000, 1024, 1]),
+    (1025, [4096, 4097, 20481, 7]),
+    (4096, [8192, 16385, 4095]),
+    (4097, [9000, 4097, 4098, 50]),
+])
+def test_lag_correlations_at_the_transforms_edges(lam, lens):
+    """Lag correlations against direct sums in extended precision, for bands on either side of
+    each transform length and intervals around the block and workgroup edges, with u and v of
+    very different size.  Bar: rounding of N-point transforms, 4 eps log2(N) ||u|| ||v||."""
+    off = np.concatenate([[0], np.cumsum(lens)])
+    n = int(off[-1])
+    pix = torch.arange(n, dtype=torch.int32, device="cuda") % 5
+    psd = np.tile([1.0, 0.0, 1.0], (len(lens), 1))
+    plan = Plan(pix, None, 5, off, psd, n_stokes=1, lam=lam, rcond_min=0.0)
+    r = np.random.default_rng(lam)
+    u = 1e-9 * (r.standard_normal(n) + np.sin(0.01 * np.arange(n)))
+    v = r.standard_normal(n) + 0.05 * np.cumsum(r.standard_normal(n))
+    c = plan.lag_correlations(torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda()).cpu().numpy()
+    for j, m in enumerate(lens):
+        U, V = (a[off[j]:off[j + 1]].astype(np.longdouble) for a in (u, v))
+        K = min(lam, m - 1)
+        ks = np.unique(np.r_[0:min(K, 8) + 1, np.linspace(0, K, 40).astype(int)])
+        ex = np.array([(U * V).sum() if k == 0 else (U[:-k] * V[k:] + U[k:] * V[:-k]).sum()
+                       for k in ks])
+        bar = 4 * 2.2e-16 * 13 * float(np.sqrt((U * U).sum() * (V * V).sum()))
+        assert np.abs(c[j, ks] - ex).max() <= bar, (lam, m)
+        assert not c[j, K + 1:].any()
+    plan.close()
