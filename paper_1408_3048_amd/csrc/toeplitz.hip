@@ -92,7 +92,8 @@ __global__ void k_twiddles(int64_t count, int64_t n, double* __restrict__ tw64,
 
 // out[g][j] = sum_{i < cnt[g]} a[g][i] cos(2 pi i j / n[g]) for j < J[g].
 // The cosine of every term comes from a rotation recurrence re-anchored by
-// sincospi every 32 terms (bounded rounding growth).
+// sincospi every 32 terms, and the terms are added in runs of 32, of 256 and of the rest
+// (bounded rounding growth).
 constexpr int kCtThreads = 256;
 __global__ void k_cos_transform(const double* __restrict__ a, const int64_t* __restrict__ aoff,
                                 const int64_t* __restrict__ acnt, const int64_t* __restrict__ nper,
@@ -115,19 +116,23 @@ __global__ void k_cos_transform(const double* __restrict__ a, const int64_t* __r
         __syncthreads();
         sa[threadIdx.x] = (i0 + threadIdx.x < cnt) ? ag[i0 + threadIdx.x] : 0.0;
         __syncthreads();
+        double chunk = 0.0;
         for (int s = 0; s < kCtThreads; s += 32) {
             if (i0 + s >= cnt) break;
             const int64_t idx = ((i0 + s) % n) * jm % n;
             double c, sn;
             sincospi(2.0 * (double)idx / (double)n, &sn, &c);
+            double run = 0.0;
 #pragma unroll 8
             for (int u = 0; u < 32; ++u) {
-                acc = fma(sa[s + u], c, acc);
+                run = fma(sa[s + u], c, run);
                 const double c2 = c * cs - sn * ss;
                 sn = fma(sn, cs, c * ss);
                 c = c2;
             }
+            chunk += run;
         }
+        acc += chunk;
     }
     if (j < J) out[ooff[g] + j] = acc;
 }
@@ -631,14 +636,15 @@ __global__ __launch_bounds__(NT) void k_spec_fft(const double* __restrict__ taps
 // taps by decimation in time: for an interval of n = R * 2M samples,
 //   t_k = (1/n) sum_{b<R} Re[ e^{2 pi i b k / n} conj(X_b(k)) ],  X_b = real DFT over a of
 //   Q(R a + b), Q(m) = q(min(m, n - m)) the inverse PSD on the interval's grid.
-// Block (b, g) writes Re[...] for k <= K to part[g][b][k]; k_taps_sum adds over b.
+// Block (b, g) writes Re[...] for k <= K to row poff[g] + b of part; k_taps_sum adds over b.
 template <int LOGM, int NT>
 __global__ __launch_bounds__(NT) void k_taps_fft(const int32_t* __restrict__ kid,
                                                  const int32_t* __restrict__ klen,
                                                  const double* __restrict__ kpar,
                                                  const int64_t* __restrict__ tcnt, double f_samp,
                                                  const double* __restrict__ tw, int kstride,
-                                                 int rmax, double* __restrict__ part, int what) {
+                                                 const int64_t* __restrict__ poff,
+                                                 double* __restrict__ part, int what) {
     constexpr int M = 1 << LOGM, NR = 2 * M;
     __shared__ __align__(16) unsigned char smem[2 * M * sizeof(double)];
     const CBuf<double> buf = make_cbuf<double>(smem, M);
@@ -657,7 +663,7 @@ __global__ __launch_bounds__(NT) void k_taps_fft(const int32_t* __restrict__ kid
     __syncthreads();
     fwd_passes<double, LOGM, NT, LOGM>(buf, tw);
     const int K = (int)tcnt[g] - 1;
-    double* out = part + ((int64_t)gi * rmax + b) * kstride;
+    double* out = part + (poff[gi] + b) * kstride;
     real_dft_out<LOGM, NT>(buf, tw, K, [&](int k, double xr, double xi) {
         double sn, cs;
         sincospi(2.0 * (double)((int64_t)b * k % n) / (double)n, &sn, &cs);
@@ -665,24 +671,120 @@ __global__ __launch_bounds__(NT) void k_taps_fft(const int32_t* __restrict__ kid
     });
 }
 
+// taps of kernel kid[gi] = window / n times the sum of its partial rows [poff[gi],
+// poff[gi + 1]) of part, in order
 __global__ void k_taps_sum(const int32_t* __restrict__ kid, const int32_t* __restrict__ klen,
                            const int64_t* __restrict__ toff, const int64_t* __restrict__ tcnt,
-                           const double* __restrict__ part, int kstride, int rmax, int lam,
-                           int window, double* __restrict__ t, int nr) {
+                           const double* __restrict__ part, int kstride,
+                           const int64_t* __restrict__ poff, int lam, int window,
+                           double* __restrict__ t) {
     const int gi = blockIdx.y;
     const int g = kid[gi];
     const int64_t n = klen[g];
-    const int R = (int)(n / nr);
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < tcnt[g];
          k += (int64_t)gridDim.x * blockDim.x) {
         double s = 0.0;
-        for (int b = 0; b < R; ++b) s += part[((int64_t)gi * rmax + b) * kstride + k];
+        for (int64_t b = poff[gi]; b < poff[gi + 1]; ++b) s += part[b * kstride + k];
         t[toff[g] + k] = s * window_at(k, lam, window) / (double)n;
+    }
+}
+
+// Taps of any interval length n by chirp transforms (Bluestein 1970: m k = (m^2 + k^2 -
+// (k - m)^2) / 2 turns a DFT at n points into a convolution).  The cosine sum over the
+// frequencies m = 0 .. n/2 is cut into segments of M - K frequencies; with m = m0 + i,
+//   sum_i a_{m0+i} e^{-2 pi i (m0 + i) k / n} = e^{-pi i (k^2 + 2 m0 k) / n}
+//       sum_i (a_{m0+i} e^{-pi i i^2 / n}) e^{pi i (k - i)^2 / n},   k = 0 .. K,
+// one circular convolution of M points per segment with a chirp that depends on n alone
+// (k_czt_chirp: its transform, one block per length).  Phases are reduced mod 2n in integers.
+// The direct sums (k_cos_transform) cost n/2 rotations per lag.  Whole FP64 plan of 256
+// intervals of distinct length, direct / chirps: about 40009 samples and 2049 lags 4.99 / 1.86
+// ms, 8195 samples 1.72 / 1.08; error of the taps against extended precision, relative to
+// their norm, 0.7-6.8e-15 / 0.2-6.4e-16.
+struct CztSeg {
+    int32_t g;      // kernel
+    int32_t chirp;  // its length's chirp
+    int64_t m0;     // first frequency
+};
+
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_czt_chirp(const int32_t* __restrict__ len, int lam,
+                                                  const double* __restrict__ tw,
+                                                  double2* __restrict__ chirp) {
+    constexpr int M = 1 << LOGM;
+    __shared__ __align__(16) unsigned char smem[2 * M * sizeof(double)];
+    const CBuf<double> buf = make_cbuf<double>(smem, M);
+    const int64_t n = len[blockIdx.x];
+    const int K = (int)(n - 1 < lam ? n - 1 : lam);
+    for (int i = threadIdx.x; i < M; i += NT) {
+        const int64_t d = i <= K ? i : M - i;  // |k - i|: lags up to K, and the M - K - 1 below 0
+        double sn, cs;
+        sincospi((double)(d * d % (2 * n)) / (double)n, &sn, &cs);
+        buf.put(i, cs, sn);
+    }
+    __syncthreads();
+    fwd_passes<double, LOGM, NT, LOGM>(buf, tw);
+    double2* out = chirp + (int64_t)blockIdx.x * M;
+    for (int i = threadIdx.x; i < M; i += NT) {  // in the order of the forward transform
+        double2 z;
+        buf.get(i, z.x, z.y);
+        out[i] = z;
+    }
+}
+
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_taps_czt(const CztSeg* __restrict__ seg,
+                                                 const int32_t* __restrict__ klen,
+                                                 const double* __restrict__ kpar, int lam,
+                                                 double f_samp, const double* __restrict__ tw,
+                                                 const double2* __restrict__ chirp, int kstride,
+                                                 double* __restrict__ part, int what) {
+    constexpr int M = 1 << LOGM;
+    __shared__ __align__(16) unsigned char smem[2 * M * sizeof(double)];
+    const CBuf<double> buf = make_cbuf<double>(smem, M);
+    const CztSeg sg = seg[blockIdx.x];
+    const int64_t n = klen[sg.g];
+    const int K = (int)(n - 1 < lam ? n - 1 : lam);
+    const double sigma = kpar[3 * sg.g], fk = kpar[3 * sg.g + 1], al = kpar[3 * sg.g + 2];
+    for (int i = threadIdx.x; i < M; i += NT) {
+        const int64_t m = sg.m0 + i;
+        double re = 0.0, im = 0.0;
+        if (i < M - K && 2 * m <= n) {
+            const double a = (m == 0 || 2 * m == n ? 1.0 : 2.0) *
+                             inv_psd_at(m, n, f_samp, sigma, fk, al, what);
+            double sn, cs;
+            sincospi((double)((int64_t)i * i % (2 * n)) / (double)n, &sn, &cs);
+            re = a * cs;
+            im = -a * sn;
+        }
+        buf.put(i, re, im);
+    }
+    __syncthreads();
+    fwd_passes<double, LOGM, NT, LOGM>(buf, tw);
+    const double2* ch = chirp + (int64_t)sg.chirp * M;
+    for (int i = threadIdx.x; i < M; i += NT) {
+        const double2 z = ch[i];
+        double re, im;
+        buf.get(i, re, im);
+        buf.put(i, re * z.x - im * z.y, re * z.y + im * z.x);
+    }
+    __syncthreads();
+    inv_passes<double, LOGM, NT, LOGM>(buf, tw);
+    double* out = part + (int64_t)blockIdx.x * kstride;
+    for (int k = threadIdx.x; k <= K; k += NT) {
+        double sn, cs, re, im;
+        sincospi((double)((int64_t)k * (k + 2 * sg.m0) % (2 * n)) / (double)n, &sn, &cs);
+        buf.get(k, re, im);
+        out[k] = (cs * re + sn * im) * (1.0 / M);
     }
 }
 
 constexpr int kPlanLogM = 13;  // plan-time FP64 FFTs: n_r = 16384 real points
 constexpr int kPlanNT = 512;
+// taps by chirp transforms: from 4096 samples, for lags that leave a segment at least a
+// quarter of the transform.  Plans of 256 intervals of about 4097 samples take, direct /
+// chirps, 1.33 / 1.06 ms at 2049 lags and 1.04 / 1.03 at 65, of 2001 samples 1.00 / 0.98; a
+// single interval of 4097 samples takes 0.82 / 0.85 and of 8195 0.88 / 0.88
+constexpr int64_t kCztMinLen = 4096, kCztMaxLag = 6144;
 
 template <typename T, int LOGM>
 int launch_logm(const ToepArgs<T>& a_in, int64_t n_tiles, hipStream_t st) {
@@ -797,6 +899,14 @@ int64_t count_tiles(const std::vector<int64_t>& off, int64_t lmax) {
 
 // ------------------------------------------------------------------ host: kernels
 
+// tw[q] = exp(-2 pi i q / n), q < count, as (re, im) pairs
+int fft_twiddles(mm_plan_t pl, int64_t count, int64_t n, double* tw) {
+    hipLaunchKernelGGL(k_twiddles, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, pl->stream,
+                       count, n, tw, (float*)nullptr);
+    MM_HIP(hipGetLastError());
+    return MM_OK;
+}
+
 // Windowed taps t_0..t_K of every distinct kernel (what = 0) or of the derivative of the
 // inverse PSD with respect to sigma, f_knee or alpha (what = 1, 2, 3), on the host, flat
 // with offsets toff and counts tcnt [App. D: the Toeplitz row is the inverse DFT of the
@@ -812,15 +922,21 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
     std::vector<double> kpar(3 * nk);
     int64_t atot = 0, ttot = 0;
     int64_t amax = 0;
-    constexpr int64_t kNs = (int64_t)2 << kPlanLogM;
-    std::vector<int32_t> fft_ids;
+    constexpr int64_t kNs = (int64_t)2 << kPlanLogM, kCz = (int64_t)1 << kPlanLogM;
+    // lengths that are multiples of the plan-time transform by decimation in time, other long
+    // ones by chirp transforms, short ones by direct sums
+    std::vector<int32_t> fft_ids, czt_ids;
+    bool direct = false;
     for (int g = 0; g < nk; ++g) {
         const int64_t n = pl->h_kern_len[g];
         const int64_t K = std::min<int64_t>(lam, n - 1);
         const bool by_fft = n % kNs == 0 && K < kNs / 2;
+        const bool by_czt = !by_fft && n >= kCztMinLen && K <= kCztMaxLag;
         if (by_fft) fft_ids.push_back(g);
+        else if (by_czt) czt_ids.push_back(g);
+        else direct = true;
         aoff[g] = atot;
-        acnt[g] = by_fft ? 0 : n / 2 + 1;
+        acnt[g] = by_fft || by_czt ? 0 : n / 2 + 1;
         atot += acnt[g];
         amax = std::max(amax, acnt[g]);
         nper[g] = n;
@@ -853,7 +969,7 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
     MM_HIP(hipMemcpyAsync(d_jcnt.p, jcnt.data(), nk * 8, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(d_toff.p, toff.data(), nk * 8, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(d_tcnt.p, tcnt.data(), nk * 8, hipMemcpyHostToDevice, st));
-    {
+    if (direct) {
         const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((amax + 255) / 256, 1024));
         hipLaunchKernelGGL(k_inv_psd, dim3(gx, nk), dim3(256), 0, st, d_klen.p, d_kpar.p,
                            d_aoff.p, d_acnt.p, pl->opts.f_samp, d_a.p, nk, what);
@@ -868,40 +984,83 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
                            pl->opts.window, nk);
         MM_HIP(hipGetLastError());
     }
+    DBuf<double> d_tw, d_part, d_part_c;
+    DBuf<int32_t> d_kid, d_kid_c, d_clen;
+    DBuf<int64_t> d_poff, d_poff_c;
+    DBuf<CztSeg> d_seg;
+    DBuf<double2> d_chirp;
+    if (!fft_ids.empty() || !czt_ids.empty()) {
+        MM_TRY(d_tw.alloc(kNs));
+        MM_TRY(fft_twiddles(pl, kNs / 2, kNs, d_tw.p));
+    }
+    // partial rows [poff[i], poff[i + 1]) of the kernels ids, added into their taps
+    auto sum_rows = [&](const std::vector<int32_t>& ids, const std::vector<int64_t>& poff,
+                        DBuf<int32_t>& kid, DBuf<int64_t>& po) -> int {
+        MM_TRY(kid.alloc(ids.size()));
+        MM_TRY(po.alloc(poff.size()));
+        MM_HIP(hipMemcpyAsync(kid.p, ids.data(), ids.size() * 4, hipMemcpyHostToDevice, st));
+        MM_HIP(hipMemcpyAsync(po.p, poff.data(), poff.size() * 8, hipMemcpyHostToDevice, st));
+        return MM_OK;
+    };
     if (!fft_ids.empty()) {
-        // decimation-in-time FFT path for interval lengths that are multiples of 2^(kPlanLogM+1)
         const int nf = (int)fft_ids.size();
         int rmax = 1, kmax = 1;
+        std::vector<int64_t> poff(1, 0);
         for (int g : fft_ids) {
-            rmax = std::max<int>(rmax, (int)(pl->h_kern_len[g] / kNs));
+            const int R = (int)(pl->h_kern_len[g] / kNs);
+            poff.push_back(poff.back() + R);
+            rmax = std::max(rmax, R);
             kmax = std::max<int>(kmax, (int)tcnt[g]);
         }
-        DBuf<double> d_tw, d_part;
-        DBuf<int32_t> d_kid;
-        MM_TRY(d_tw.alloc(kNs));
-        MM_TRY(d_kid.alloc(nf));
-        MM_TRY(d_part.alloc((size_t)nf * rmax * kmax));
-        hipLaunchKernelGGL(k_twiddles, dim3((kNs / 2 + 255) / 256), dim3(256), 0, st, kNs / 2,
-                           kNs, d_tw.p, (float*)nullptr);
-        MM_HIP(hipMemcpyAsync(d_kid.p, fft_ids.data(), nf * 4, hipMemcpyHostToDevice, st));
+        MM_TRY(sum_rows(fft_ids, poff, d_kid, d_poff));
+        MM_TRY(d_part.alloc((size_t)poff[nf] * kmax));
         hipLaunchKernelGGL((k_taps_fft<kPlanLogM, kPlanNT>), dim3(rmax, nf), dim3(kPlanNT), 0, st,
                            d_kid.p, d_klen.p, d_kpar.p, d_tcnt.p, pl->opts.f_samp, d_tw.p, kmax,
-                           rmax, d_part.p, what);
+                           d_poff.p, d_part.p, what);
         MM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, nf), dim3(256), 0, st, d_kid.p,
-                           d_klen.p, d_toff.p, d_tcnt.p, d_part.p, kmax, rmax, lam,
-                           pl->opts.window, d_t.p, (int)kNs);
+                           d_klen.p, d_toff.p, d_tcnt.p, d_part.p, kmax, d_poff.p, lam,
+                           pl->opts.window, d_t.p);
+        MM_HIP(hipGetLastError());
+    }
+    if (!czt_ids.empty()) {
+        const int nf = (int)czt_ids.size();
+        int kmax = 1;
+        std::vector<int64_t> poff(1, 0);
+        std::vector<CztSeg> seg;
+        std::map<int32_t, int32_t> of_len;  // interval length -> chirp
+        std::vector<int32_t> lens;
+        for (int g : czt_ids) {
+            const int32_t n = pl->h_kern_len[g];
+            const auto it = of_len.emplace(n, (int32_t)lens.size());
+            if (it.second) lens.push_back(n);
+            const int64_t step = kCz - (tcnt[g] - 1);
+            for (int64_t m0 = 0; m0 <= n / 2; m0 += step) seg.push_back({g, it.first->second, m0});
+            poff.push_back((int64_t)seg.size());
+            kmax = std::max<int>(kmax, (int)tcnt[g]);
+        }
+        MM_TRY(sum_rows(czt_ids, poff, d_kid_c, d_poff_c));
+        MM_TRY(d_seg.alloc(seg.size()));
+        MM_TRY(d_clen.alloc(lens.size()));
+        MM_TRY(d_chirp.alloc(lens.size() * kCz));
+        MM_TRY(d_part_c.alloc(seg.size() * kmax));
+        MM_HIP(hipMemcpyAsync(d_seg.p, seg.data(), seg.size() * sizeof(CztSeg),
+                              hipMemcpyHostToDevice, st));
+        MM_HIP(hipMemcpyAsync(d_clen.p, lens.data(), lens.size() * 4, hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL((k_czt_chirp<kPlanLogM, kPlanNT>), dim3((unsigned)lens.size()),
+                           dim3(kPlanNT), 0, st, d_clen.p, lam, d_tw.p, d_chirp.p);
+        MM_HIP(hipGetLastError());
+        hipLaunchKernelGGL((k_taps_czt<kPlanLogM, kPlanNT>), dim3((unsigned)seg.size()),
+                           dim3(kPlanNT), 0, st, d_seg.p, d_klen.p, d_kpar.p, lam,
+                           pl->opts.f_samp, d_tw.p, (const double2*)d_chirp.p, kmax, d_part_c.p,
+                           what);
+        MM_HIP(hipGetLastError());
+        hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, nf), dim3(256), 0, st, d_kid_c.p,
+                           d_klen.p, d_toff.p, d_tcnt.p, d_part_c.p, kmax, d_poff_c.p, lam,
+                           pl->opts.window, d_t.p);
         MM_HIP(hipGetLastError());
     }
     // the temporaries above are released in stream order after the kernels that read them
-    return MM_OK;
-}
-
-// tw[q] = exp(-2 pi i q / n), q < count, as (re, im) pairs
-int fft_twiddles(mm_plan_t pl, int64_t count, int64_t n, double* tw) {
-    hipLaunchKernelGGL(k_twiddles, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, pl->stream,
-                       count, n, tw, (float*)nullptr);
-    MM_HIP(hipGetLastError());
     return MM_OK;
 }
 

@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
+import oracle as O  # noqa: E402
 import synth  # noqa: E402
 from paper_1408_3048_amd import Plan  # noqa: E402
 
@@ -89,4 +90,40 @@ def test_lag_correlations_at_the_transforms_edges(lam, lens):
         bar = 4 * 2.2e-16 * 13 * float(np.sqrt((U * U).sum() * (V * V).sum()))
         assert np.abs(c[j, ks] - ex).max() <= bar, (lam, m)
         assert not c[j, K + 1:].any()
+    plan.close()
+
+
+@pytest.mark.parametrize("lam,lens", [
+    (0, [4096, 4097, 100]),
+    (300, [4095, 4096, 4097, 16383, 16384, 16385, 32768]),
+    (1000, [14382, 14383, 14384, 28768, 28769]),  # one segment / two, two / three
+    (6144, [12289, 16385, 40001, 4100]),
+    (6145, [12291, 16386]),                       # direct sums
+])
+def test_taps_of_any_interval_length(lam, lens):
+    """Taps and their derivatives of long intervals (chirp transforms) and on either side of
+    their lines, against the oracle's inverse DFT.  Bar: rounding of two 8192-point transforms
+    in the norm of the inverse PSD, and of its evaluation."""
+    off = np.concatenate([[0], np.cumsum(lens)])
+    n_t = int(off[-1])
+    r = np.random.default_rng(lam)
+    psd = np.stack([r.uniform(0.5, 2.0, len(lens)), r.uniform(2.0, 4.0, len(lens)),
+                    r.uniform(1.0, 2.0, len(lens))], 1)
+    psd[1, 1] = 0.0  # white noise
+    plan = Plan(torch.arange(n_t, dtype=torch.int32, device="cuda") % 512, None, 512, off, psd,
+                n_stokes=1, lam=lam, window="gauss", rcond_min=0.0, fft_len_f64=16384)
+    dt = plan.tap_derivatives()
+    eps = 2.2e-16
+    for j, n in enumerate(lens):
+        q = O.inverse_psd(n, *psd[j], 200.0)
+        D = O.tap_derivatives(n, *psd[j], lam, 200.0)
+        K = min(lam, n - 1)
+        unit = (208 * eps * np.linalg.norm(q) + 32 * eps * np.abs(q).sum()) / n
+        t = plan.interval_taps(j)
+        assert t.shape == (K + 1,)
+        assert np.abs(t - O.toeplitz_taps(n, *psd[j], lam, 200.0)).max() <= unit, (lam, n)
+        # |dq| <= 2 q / sigma, alpha q / (2 f_knee)... and q |log(f_knee / f)| for f down to 1/n
+        big = np.array([2 / psd[j, 0], psd[j, 2] / max(psd[j, 1], 0.5), np.log(200.0 * n)])
+        assert (np.abs(dt[j, :, :K + 1] - D).max(1) <= 2 * unit * big).all(), (lam, n)
+        assert not dt[j, :, K + 1:].any()
     plan.close()
