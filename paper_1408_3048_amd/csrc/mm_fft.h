@@ -106,18 +106,30 @@ __device__ __forceinline__ int rev_bits(int v) {
     return (int)(__builtin_bitreverse32((uint32_t)v) >> (32 - BITS));
 }
 
-// exp(-2 pi i q / 16), q = 0..15
+// exp(-2 pi i e / 32), e = 0..15: the constants of the networks, and the twiddles of a
+// radix-16 pass of block size 32 for its group k = 1 (cos and sin of multiples of pi/16)
 template <typename T>
-__device__ __forceinline__ void root16(int q, T& c, T& s) {
-    constexpr double C1 = 0.92387953251128675613, S1 = 0.38268343236508977173,
-                     C2 = 0.70710678118654752440;
-    const double cs[16] = {1.0, C1, C2, S1, 0.0, -S1, -C2, -C1, -1.0, -C1, -C2, -S1, 0.0, S1, C2, C1};
-    const double sn[16] = {0.0, S1, C2, C1, 1.0, C1, C2, S1, 0.0, -S1, -C2, -C1, -1.0, -C1, -C2, -S1};
-    c = (T)cs[q & 15];
-    s = (T)(-sn[q & 15]);
+__device__ __forceinline__ void root32(int e, T& c, T& s) {
+    // cos and sin of pi e / 16
+    constexpr double cs[16] = {1.0, 0.98078528040323044913, 0.92387953251128675613,
+                               0.83146961230254523708, 0.70710678118654752440,
+                               0.55557023301960222474, 0.38268343236508977173,
+                               0.19509032201612826785, 0.0, -0.19509032201612826785,
+                               -0.38268343236508977173, -0.55557023301960222474,
+                               -0.70710678118654752440, -0.83146961230254523708,
+                               -0.92387953251128675613, -0.98078528040323044913};
+    constexpr double sn[16] = {0.0, 0.19509032201612826785, 0.38268343236508977173,
+                               0.55557023301960222474, 0.70710678118654752440,
+                               0.83146961230254523708, 0.92387953251128675613,
+                               0.98078528040323044913, 1.0, 0.98078528040323044913,
+                               0.92387953251128675613, 0.83146961230254523708,
+                               0.70710678118654752440, 0.55557023301960222474,
+                               0.38268343236508977173, 0.19509032201612826785};
+    c = (T)cs[e & 15];
+    s = (T)(-sn[e & 15]);
 }
 
-// in-register radix-R DIF network: natural in, bit-reversed out (forward, e^{-i})
+// in-register radix-R DIF network (R <= 32): natural in, bit-reversed out (forward, e^{-i})
 template <typename T, int R>
 __device__ __forceinline__ void dif_net(T* vr, T* vi) {
 #pragma unroll
@@ -131,16 +143,16 @@ __device__ __forceinline__ void dif_net(T* vr, T* vi) {
                 vr[b + kk] = ar + cr;
                 vi[b + kk] = ai + ci;
                 const T dr = ar - cr, di = ai - ci;
-                const int q = kk * (16 / (2 * h));
-                if (q == 0) {
+                const int e = kk * (16 / h);  // exp(-2 pi i kk / 2h) = exp(-2 pi i e / 32)
+                if (e == 0) {
                     vr[b + kk + h] = dr;
                     vi[b + kk + h] = di;
-                } else if (q == 4) {  // * (-i)
+                } else if (e == 8) {  // * (-i)
                     vr[b + kk + h] = di;
                     vi[b + kk + h] = -dr;
                 } else {
                     T c, s;
-                    root16<T>(q, c, s);
+                    root32<T>(e, c, s);
                     vr[b + kk + h] = dr * c - di * s;
                     vi[b + kk + h] = dr * s + di * c;
                 }
@@ -158,15 +170,15 @@ __device__ __forceinline__ void dit_net_inv(T* vr, T* vi) {
         for (int b = 0; b < R; b += 2 * h) {
 #pragma unroll
             for (int kk = 0; kk < h; ++kk) {
-                const int q = kk * (16 / (2 * h));
+                const int e = kk * (16 / h);
                 T cr = vr[b + kk + h], ci = vi[b + kk + h];
-                if (q == 4) {  // * (+i)
+                if (e == 8) {  // * (+i)
                     const T t = cr;
                     cr = -ci;
                     ci = t;
-                } else if (q != 0) {
+                } else if (e != 0) {
                     T c, s;
-                    root16<T>(q, c, s);
+                    root32<T>(e, c, s);
                     s = -s;  // conjugate root
                     const T t = cr * c - ci * s;
                     ci = cr * s + ci * c;
@@ -204,29 +216,6 @@ __device__ __forceinline__ void powers(T wr, T wi, T* pr, T* pi) {
 // part) at swizzled position p sits at byte 8 p, and swz is linear over XOR, so the
 // byte offset of point (base + c) is (8 swz(base)) ^ (8 swz(c)) for bit-disjoint base and
 // c: one XOR with a compile-time constant per point.
-// exp(-2 pi i e / 32), e = 0..15: the twiddles of a radix-16 pass of block size 32 for its
-// group k = 1 (cos and sin of multiples of pi/16)
-template <typename T>
-__device__ __forceinline__ void root32(int e, T& c, T& s) {
-    // cos and sin of pi e / 16
-    constexpr double cs[16] = {1.0, 0.98078528040323044913, 0.92387953251128675613,
-                               0.83146961230254523708, 0.70710678118654752440,
-                               0.55557023301960222474, 0.38268343236508977173,
-                               0.19509032201612826785, 0.0, -0.19509032201612826785,
-                               -0.38268343236508977173, -0.55557023301960222474,
-                               -0.70710678118654752440, -0.83146961230254523708,
-                               -0.92387953251128675613, -0.98078528040323044913};
-    constexpr double sn[16] = {0.0, 0.19509032201612826785, 0.38268343236508977173,
-                               0.55557023301960222474, 0.70710678118654752440,
-                               0.83146961230254523708, 0.92387953251128675613,
-                               0.98078528040323044913, 1.0, 0.98078528040323044913,
-                               0.92387953251128675613, 0.83146961230254523708,
-                               0.70710678118654752440, 0.55557023301960222474,
-                               0.38268343236508977173, 0.19509032201612826785};
-    c = (T)cs[e & 15];
-    s = (T)(-sn[e & 15]);
-}
-
 // Twiddles of a pass (block size B = 2^LOGB, Q = B / 2^LR groups per block):
 //  - Q == 2 (B = 32): the groups are mapped so that every wave has one k; k = 0 needs none,
 //    k = 1 the constants root32;

@@ -95,11 +95,14 @@ __host__ __device__ inline int64_t xcd_item(int64_t b, int64_t n) {
 struct FftTiling {
     int logm = 0;            // complex half-length M = 2^logm, real length n_r = 2M
     int n_r = 0;
+    bool paired = false;     // tiles 2p and 2p + 1, of one interval, go through one transform of
+                             // n_r complex points (the second may be empty)
     int64_t n_tiles = 0;
     DBuf<int64_t> tile_out;  // first output sample of every tile
     DBuf<int32_t> tile_len;  // outputs of every tile
     DBuf<int32_t> tile_int;  // interval of every tile
-    DBuf<double> H64;        // [n_kern][M+1] kernel spectrum / n_r, FP64 operator
+    DBuf<double> H64;        // [n_kern][M+1] kernel spectrum / n_r, FP64 operator; paired:
+                             // [n_kern][n_r] in the order of k_toeplitz_pair
     DBuf<float> H32;         // same, FP32 operator
     DBuf<double> tw64;       // [n_r/2][2] exp(-2 pi i q / n_r)
     DBuf<float> tw32;

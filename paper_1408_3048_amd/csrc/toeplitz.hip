@@ -26,7 +26,7 @@
 #include <tuple>
 #include <type_traits>
 
-#include "mm_fft.h"
+#include "mm_fft_reg.h"
 
 namespace mm {
 namespace {
@@ -578,6 +578,245 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
             buf.get_part(i >> 1, i & 1);
 }
 
+// ---- FP64, two tiles per workgroup, in registers
+//
+// The kernel spectrum H is real and even, so the band convolution of y_a + i y_b, two windows
+// of one interval as one complex sequence of N = n_r points, leaves y_a's result in the real
+// part and y_b's in the imaginary part: the spectrum product is one real factor per point,
+// without the split, twiddles and partner access that a packed real transform needs.  The
+// transform is RegFft's: a thread loads point t + NT i of both windows straight into its
+// registers (samples of consecutive threads are consecutive), and stores its results from
+// there; LDS carries the two exchanges each way alone.  H is stored in the order the threads
+// hold the bit-reversed spectrum, two values per thread and load.
+//
+// What bounded the LDS-resident FP64 tile was the latency of its passes at 2 waves per SIMD
+// (a complex buffer of 64 KB per tile); here 4 are resident.  N^-1 of a TOD / N^-1 P x, in us,
+// LDS-resident / in registers: 2^20 samples, lambda = 2048 30.7 / 18.5 and 36 / 28; 2^22 58 / 33
+// and 67 / 50; 2^24 172 / 121 and 214 / 181; lambda = 512, 5.8e6 samples in ragged intervals
+// 49.0 / 35.6 and 64 / 53; 2^18 samples of one Stokes parameter, lambda = 1024 11.1 / 11.1 and
+// 13.2 / 11.4.  The map gather is what is left beside the transform: its loads and the
+// transforms of a CU's two workgroups overlap little.  The error against 64-bit FFTs of
+// whole intervals fell from 1.0e-15 to 0.6e-15 (twiddle powers rounded once).
+//
+// The same kernel in FP32 (32 points per thread) gained nothing at 16384 points (raster of
+// 2^24: 94.5 / 96.5 us, ring scan of 2^25: 229 / 235) and lost at 8192 and below 2^23 samples
+// (half as many workgroups): FP32 keeps the LDS-resident tile.
+
+// vr[i], vi[i] = sample t + NT i of the two windows, 0 outside their interval, BP samples at a
+// time alternating between the windows; nz: whether any is nonzero
+template <int R, int NT, int MODE>
+__device__ __forceinline__ void load_pair(const ToepArgs<double>& a, const int64_t (&base)[2],
+                                          const int (&i_lo)[2], const int (&i_hi)[2], double* vr,
+                                          double* vi, bool (&nz)[2]) {
+    // one-value loads: a window's 16 together
+    constexpr int BP = MODE == 0 ? 4 : R, NB = 2 * R / BP;
+    nz[0] = nz[1] = false;
+    // sample u of batch q: window q & 1, point (q / 2) BP + u; samples outside read position
+    // i_lo, inside the interval
+    auto pos = [&](int q, int u) -> uint32_t {
+        const int w = q & 1, i = threadIdx.x + ((q >> 1) * BP + u) * NT;
+        return (uint32_t)(i >= i_lo[w] && i < i_hi[w] ? i : i_lo[w]);
+    };
+    auto put = [&](int q, int u, double v) {
+        const int w = q & 1, k = (q >> 1) * BP + u, i = threadIdx.x + k * NT;
+        v = i >= i_lo[w] && i < i_hi[w] ? v : 0.0;
+        asm volatile("" : "+v"(v));  // formed here, not where it is used
+        (w ? vi : vr)[k] = v;
+        nz[w] = nz[w] || v != 0.0;
+    };
+    if constexpr (MODE == 0) {
+        // every sample's pixel index first (in the registers that the points will fill), then
+        // the weights of a batch one batch ahead of its map gathers
+        const char* xpb = reinterpret_cast<const char*>(a.xp);
+        const double2* wb = reinterpret_cast<const double2*>(a.w);
+        uint32_t cc[2 * R];
+        double2 ww[BP];
+#pragma unroll
+        for (int u = 0; u < BP; ++u) {
+            cc[u] = (uint32_t)at_u32(a.cid + base[0], pos(0, u));
+            ww[u] = at_u32(wb + base[0], pos(0, u));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 1; q < NB; ++q)
+#pragma unroll
+            for (int u = 0; u < BP; ++u)
+                cc[q * BP + u] = (uint32_t)at_u32(a.cid + base[q & 1], pos(q, u));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            double4 xx[BP];
+            double2 wc[BP];
+#pragma unroll
+            for (int u = 0; u < BP; ++u) {
+                xx[u] = *reinterpret_cast<const double4*>(xpb + cc[q * BP + u] *
+                                                                    (uint32_t)sizeof(double4));
+                wc[u] = ww[u];
+            }
+            // the gathers before the next batch's loads, so that they can be waited for alone
+            __builtin_amdgcn_sched_barrier(0);
+            if (q + 1 < NB) {
+#pragma unroll
+                for (int u = 0; u < BP; ++u)
+                    ww[u] = at_u32(wb + base[(q + 1) & 1], pos(q + 1, u));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < BP; ++u)
+                put(q, u, xx[u].x + wc[u].x * xx[u].y + wc[u].y * xx[u].z);
+        }
+    } else {
+        [[maybe_unused]] uint32_t cc[2 * R];
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+#pragma unroll
+                for (int u = 0; u < BP; ++u)
+                    cc[q * BP + u] = (uint32_t)at_u32(a.cid + base[q], pos(q, u));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            double v[BP];
+#pragma unroll
+            for (int u = 0; u < BP; ++u) {
+                if constexpr (MODE == 1) v[u] = a.x[cc[q * BP + u]];
+                else if constexpr (MODE == 2) v[u] = at_u32((const double*)a.y + base[q], pos(q, u));
+                else v[u] = (double)at_u32((const float*)a.y + base[q], pos(q, u));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < BP; ++u) put(q, u, v[u]);
+        }
+    }
+}
+
+// launch bounds: 16 waves per CU (128 registers), which both lengths' LDS allows
+template <int LOGN, int MODE, bool SKIPZ>
+__global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<double> a) {
+    using F = RegFft<LOGN>;
+    constexpr int R = F::R, NT = F::NT;
+    __shared__ __align__(16) double s[F::ELEMS];
+    const int64_t pair = SKIPZ ? (int64_t)blockIdx.x : xcd_item(blockIdx.x, a.n_tiles);
+    if (pair < 0 || pair >= a.n_tiles) return;
+    const int j = a.tile_int[2 * pair];
+    if (a.mask && !a.mask[a.int_prob[j]]) return;
+    const int64_t o[2] = {a.tile_out[2 * pair], a.tile_out[2 * pair + 1]};
+    const int L[2] = {a.tile_len[2 * pair], a.tile_len[2 * pair + 1]};  // L[1] may be 0
+    const int64_t lo = a.int_lo[j], hi = a.int_hi[j];
+    const int lam = a.lam, t = threadIdx.x;
+    if constexpr (SKIPZ) {
+        if (a.int_on && !a.int_on[j]) {
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                for (int i = t; i < L[w]; i += NT) a.z[o[w] + i] = 0.0;
+            return;
+        }
+    }
+    const int64_t base[2] = {o[0] - lam, o[1] - lam};
+    int i_lo[2], i_hi[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const int win = L[w] ? L[w] + 2 * lam : 0;
+        i_lo[w] = (int)(lo > base[w] ? lo - base[w] : 0);
+        i_hi[w] = (int)(hi - base[w] < (int64_t)win ? hi - base[w] : (int64_t)win);
+    }
+    double vr[R], vi[R];
+    bool nz[2];
+    load_pair<R, NT, MODE>(a, base, i_lo, i_hi, vr, vi, nz);
+    F::pin(vr, vi);
+    // what a window's outputs are instead of the transform's: 0 for a zero window (the exact
+    // result), NaN for a window with a sample that is not finite, whose transform would be NaN
+    // throughout, and which is left out of the common one so that the other window stays clean
+    bool fixed[2] = {false, false};
+    double value[2] = {0.0, 0.0};
+    if constexpr (SKIPZ) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) fixed[w] = !__syncthreads_or(nz[w]);
+    }
+    double bad[2] = {0.0, 0.0};  // NaN where a sample is not finite
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        bad[0] = fma(vr[i], 0.0, bad[0]);
+        bad[1] = fma(vi[i], 0.0, bad[1]);
+    }
+    if (__syncthreads_or(bad[0] + bad[1] != 0.0)) {
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+            if (!__syncthreads_or(bad[w] != 0.0)) continue;
+            fixed[w] = true;
+            value[w] = __builtin_nan("");
+#pragma unroll
+            for (int i = 0; i < R; ++i) (w ? vi : vr)[i] = 0.0;
+        }
+    }
+    // without SKIPZ always taken: the transform in a block of its own keeps the compiler from
+    // moving its loads and addresses up into the load phase, whose registers they would spill
+    int go = 1;
+    if constexpr (SKIPZ) go = !(fixed[0] && fixed[1]);
+    else asm volatile("" : "+s"(go));
+    if (go) {
+        F::forward(vr, vi, s, a.tw, t);
+        F::pin(vr, vi);
+        const double2* h = reinterpret_cast<const double2*>(a.H + (int64_t)a.int_kern[j] * F::N);
+#pragma unroll
+        for (int q = 0; q < R / 2; ++q) {
+            const double2 hv = h[q * NT + t];
+            vr[2 * q] *= hv.x;
+            vi[2 * q] *= hv.x;
+            vr[2 * q + 1] *= hv.y;
+            vi[2 * q + 1] *= hv.y;
+        }
+        F::pin(vr, vi);
+        F::inverse(vr, vi, s, a.tw, F::fresh(t));
+    }
+    const int ts = F::fresh(t);
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        double* zo = a.z + o[w];
+        if (fixed[w]) {
+            for (int i = t; i < L[w]; i += NT) zo[i] = value[w];
+            continue;
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int q = ts + i * NT - lam;
+            if (q >= 0 && q < L[w])
+                *reinterpret_cast<double*>(reinterpret_cast<char*>(zo) + (uint32_t)q * 8u) =
+                    (w ? vi : vr)[i];
+        }
+    }
+}
+
+// RegFft's twiddle table of 2^logn points, 2^logr per thread
+__global__ void k_twiddles_pair(int logn, int logr, double* __restrict__ tw) {
+    const int nt = 1 << (logn - logr), q2 = nt >> logr;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < logr * (nt + q2);
+         x += gridDim.x * blockDim.x) {
+        const bool one = x < logr * nt;
+        const int y = one ? x : x - logr * nt, m = one ? nt : q2;
+        double sn, cs;
+        sincospi(-2.0 * (double)((int64_t)(y % m) << (y / m)) / (double)(one ? 1 << logn : nt), &sn,
+                 &cs);
+        tw[2 * x] = cs;
+        tw[2 * x + 1] = sn;
+    }
+}
+
+// the spectra H(f) / N in the order of k_toeplitz_pair's threads: value e of pair q of thread t
+// is position R t + 2 q + e of the bit-reversed spectrum
+__global__ void k_spec_pair(const double* __restrict__ Hraw, int logn, int logr, double scale,
+                            double* __restrict__ out) {
+    const int n = 1 << logn, r = 1 << logr, nt = n / r;
+    const double* h = Hraw + (int64_t)blockIdx.y * (n / 2 + 1);
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
+        const int e = x & 1, t = (x >> 1) % nt, q = (x >> 1) / nt;
+        const int p = r * t + 2 * q + e;
+        const int f = (int)(__builtin_bitreverse32((uint32_t)p) >> (32 - logn));
+        out[(int64_t)blockIdx.y * n + x] = h[f <= n / 2 ? f : n - f] * scale;
+    }
+}
+
 // ------------------------------------------------------------------ plan-time FFTs (FP64)
 //
 // X_m, m = 0..mmax <= M, of the real sequence packed in (re, im) after the forward
@@ -810,26 +1049,49 @@ int launch_logm(const ToepArgs<T>& a_in, int64_t n_tiles, hipStream_t st) {
     return MM_OK;
 }
 
-template <typename T>
-int launch(const ToepArgs<T>& a, int logm, int64_t n_tiles, hipStream_t st) {
-    if (n_tiles == 0) return MM_OK;
-    if constexpr (sizeof(T) == 4) {
-        switch (logm) {
-            case 10: return launch_logm<T, 10>(a, n_tiles, st);
-            case 11: return launch_logm<T, 11>(a, n_tiles, st);
-            case 12: return launch_logm<T, 12>(a, n_tiles, st);
-            case 13: return launch_logm<T, 13>(a, n_tiles, st);
-            case 14: return launch_logm<T, 14>(a, n_tiles, st);
-        }
+template <int LOGN>
+int launch_pair(const ToepArgs<double>& a_in, int64_t n_pairs, hipStream_t st) {
+    ToepArgs<double> a = a_in;
+    a.n_tiles = n_pairs;
+    const dim3 g((unsigned)xcd_grid(n_pairs)), gz((unsigned)n_pairs), nt(RegFft<LOGN>::NT);
+    if (a.skip_zero) {
+        if (a.mode == 0)
+            hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 0, true>), gz, nt, 0, st, a);
+        else
+            hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 1, true>), gz, nt, 0, st, a);
     } else {
-        switch (logm) {
-            case 10: return launch_logm<T, 10>(a, n_tiles, st);
-            case 11: return launch_logm<T, 11>(a, n_tiles, st);
-            case 12: return launch_logm<T, 12>(a, n_tiles, st);
-            case 13: return launch_logm<T, 13>(a, n_tiles, st);
+        switch (a.mode) {
+            case 0: hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 0, false>), g, nt, 0, st, a); break;
+            case 1: hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 1, false>), g, nt, 0, st, a); break;
+            case 2: hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 2, false>), g, nt, 0, st, a); break;
+            default: hipLaunchKernelGGL((k_toeplitz_pair<LOGN, 3, false>), g, nt, 0, st, a); break;
         }
     }
-    set_error("no overlap-save kernel for log2(M) = %d", logm);
+    MM_HIP(hipGetLastError());
+    return MM_OK;
+}
+
+template <typename T>
+int launch(const ToepArgs<T>& a, const FftTiling& ft, hipStream_t st) {
+    if (ft.n_tiles == 0) return MM_OK;
+    const int64_t n = ft.n_tiles;
+    if constexpr (sizeof(T) == 4) {
+        switch (ft.logm) {
+            case 10: return launch_logm<T, 10>(a, n, st);
+            case 11: return launch_logm<T, 11>(a, n, st);
+            case 12: return launch_logm<T, 12>(a, n, st);
+            case 13: return launch_logm<T, 13>(a, n, st);
+            case 14: return launch_logm<T, 14>(a, n, st);
+        }
+    } else {
+        switch (ft.logm) {
+            case 10: return launch_logm<T, 10>(a, n, st);
+            case 11: return launch_pair<12>(a, n / 2, st);
+            case 12: return launch_pair<13>(a, n / 2, st);
+            case 13: return launch_logm<T, 13>(a, n, st);
+        }
+    }
+    set_error("no overlap-save kernel for log2(M) = %d", ft.logm);
     return MM_ERR_ARG;
 }
 
@@ -889,11 +1151,21 @@ __global__ void k_gather_t0(const double* __restrict__ taps, const int64_t* __re
 constexpr int64_t kCus = 256;  // compute units of the chip
 constexpr int kMaxLogM64 = 13, kMaxLogM32 = 14, kMinLogM = 10;
 
-int64_t count_tiles(const std::vector<int64_t>& off, int64_t lmax) {
+// tiles of an interval of n samples, at most lmax outputs each
+int64_t tiles_of(int64_t n, int64_t lmax, bool paired) {
+    return paired ? 2 * ((n + 2 * lmax - 1) / (2 * lmax)) : (n + lmax - 1) / lmax;
+}
+
+int64_t count_tiles(const std::vector<int64_t>& off, int64_t lmax, bool paired) {
     int64_t n = 0;
-    for (size_t j = 0; j + 1 < off.size(); ++j) n += (off[j + 1] - off[j] + lmax - 1) / lmax;
+    for (size_t j = 0; j + 1 < off.size(); ++j) n += tiles_of(off[j + 1] - off[j], lmax, paired);
     return n;
 }
+
+// FP64 lengths n_r = 2^(l + 1) whose tiles go in pairs (k_toeplitz_pair): 4096 and 8192.  2048
+// points serve short intervals, often of one tile; 16384 points would need 128 KB of LDS, one
+// workgroup per CU, as the LDS-resident tile does, and are taken for lambda > 3072
+bool pair_length(bool fp64, int l) { return fp64 && (l == 11 || l == 12); }
 
 }  // namespace
 
@@ -1181,7 +1453,8 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
             if (lmax < nr / 4) continue;
             const int64_t tile_lds = nr * (fp64 ? 8 : 4);
             const double resident = (160 * 1024) / tile_lds >= 2 ? 1.0 : 2.0;
-            const double tiles = (double)std::max<int64_t>(count_tiles(pl->h_off, lmax), kCus);
+            const double tiles = (double)std::max<int64_t>(
+                count_tiles(pl->h_off, lmax, pair_length(fp64, l)), kCus);
             const double cost = tiles * (double)nr * (l + 5) * resident;
             if (logm == 0 || cost < best) {
                 best = cost;
@@ -1196,6 +1469,7 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
     }
     ft.logm = logm;
     ft.n_r = 2 << logm;
+    ft.paired = pair_length(fp64, logm);
     const int M = 1 << logm;
     const int64_t lmax = (int64_t)ft.n_r - 2 * (int64_t)lam;
     // balanced tiles per interval
@@ -1203,12 +1477,18 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
     std::vector<int32_t> tlen, tint;
     for (int32_t j = 0; j < pl->n_int; ++j) {
         const int64_t a = pl->h_off[j], b = pl->h_off[j + 1], n = b - a;
-        const int64_t nt = (n + lmax - 1) / lmax;
+        const int64_t nt = tiles_of(n, lmax, ft.paired);
         const int64_t len = (n + nt - 1) / nt;
         for (int64_t i = 0; i < nt; ++i) {
             const int64_t s = a + i * len;
             const int64_t e = std::min(b, s + len);
-            if (e <= s) continue;
+            if (e <= s) {
+                if (!ft.paired || i % 2 == 0) break;
+                tout.push_back(tout.back());  // an empty second tile
+                tlen.push_back(0);
+                tint.push_back(j);
+                break;
+            }
             tout.push_back(s);
             tlen.push_back((int32_t)(e - s));
             tint.push_back(j);
@@ -1221,18 +1501,18 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
     MM_HIP(hipMemcpyAsync(ft.tile_out.p, tout.data(), ft.n_tiles * 8, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(ft.tile_len.p, tlen.data(), ft.n_tiles * 4, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(ft.tile_int.p, tint.data(), ft.n_tiles * 4, hipMemcpyHostToDevice, st));
-    // twiddles exp(-2 pi i q / n_r), q < M, in FP64 (the spectra below and FP64 tiles) and
-    // FP32 for FP32 tiles
+    // twiddles exp(-2 pi i q / n_r), q < M, in FP64 (the spectra below and unpaired FP64
+    // tiles) and FP32 for FP32 tiles; pairs have a table of their own
     DBuf<double> d_tw;
     double* tw64 = nullptr;
-    if (fp64) {
+    if (fp64 && !ft.paired) {
         MM_TRY(ft.tw64.alloc(2 * M));
         tw64 = ft.tw64.p;
     } else {
         MM_TRY(d_tw.alloc(2 * M));
-        MM_TRY(ft.tw32.alloc(2 * M));
         tw64 = d_tw.p;
     }
+    if (!fp64) MM_TRY(ft.tw32.alloc(2 * M));
     hipLaunchKernelGGL(k_twiddles, dim3((M + 255) / 256), dim3(256), 0, st, (int64_t)M,
                        (int64_t)ft.n_r, tw64, fp64 ? (float*)nullptr : ft.tw32.p);
     MM_HIP(hipGetLastError());
@@ -1295,14 +1575,25 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
         MM_HIP(hipGetLastError());
     }
     const double scale = 1.0 / (double)ft.n_r;
-    if (fp64) {
+    if (ft.paired) {
+        MM_TRY(ft.H64.alloc((size_t)nk * ft.n_r));
+    } else if (fp64) {
         MM_TRY(ft.H64.alloc((size_t)nk * (M + 1)));
     } else {
         MM_TRY(ft.H32.alloc((size_t)nk * (M + 1)));
     }
     hipLaunchKernelGGL(k_spec_finish, dim3(nk), dim3(256), 0, st, d_h.p, (int64_t)(M + 1),
-                       (int64_t)(M + 1), scale, fp64 ? ft.H64.p : nullptr,
+                       (int64_t)(M + 1), scale, fp64 && !ft.paired ? ft.H64.p : nullptr,
                        fp64 ? nullptr : ft.H32.p, d_min.p);
+    if (ft.paired) {
+        constexpr int lr = RegFft<12>::LOGR;
+        const int ntw = logm == 11 ? RegFft<12>::TW : RegFft<13>::TW;
+        MM_TRY(ft.tw64.alloc(2 * ntw));
+        hipLaunchKernelGGL(k_twiddles_pair, dim3((ntw + 255) / 256), dim3(256), 0, st, logm + 1, lr,
+                           ft.tw64.p);
+        hipLaunchKernelGGL(k_spec_pair, dim3((unsigned)(ft.n_r / 256), (unsigned)nk), dim3(256), 0,
+                           st, d_h.p, logm + 1, lr, scale, ft.H64.p);
+    }
     MM_HIP(hipGetLastError());
     std::vector<double> hmin(nk);
     MM_HIP(hipMemcpyAsync(hmin.data(), d_min.p, nk * 8, hipMemcpyDeviceToHost, st));
@@ -1343,7 +1634,7 @@ int toeplitz_map64(mm_plan_t pl, const double* x, double* z, const int* mask, bo
     a.mode = pl->n_s == 3 ? 0 : 1;
     a.z = z;
     a.mask = mask;
-    return launch<double>(a, pl->fft64.logm, pl->fft64.n_tiles, pl->stream);
+    return launch<double>(a, pl->fft64, pl->stream);
 }
 
 int toeplitz_map64_i(mm_plan_t pl, const double* xi, double* z, const uint8_t* int_on) {
@@ -1353,7 +1644,7 @@ int toeplitz_map64_i(mm_plan_t pl, const double* xi, double* z, const uint8_t* i
     a.x = xi;
     a.mode = 1;
     a.z = z;
-    return launch<double>(a, pl->fft64.logm, pl->fft64.n_tiles, pl->stream);
+    return launch<double>(a, pl->fft64, pl->stream);
 }
 
 int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask, bool skip_zero,
@@ -1366,7 +1657,7 @@ int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask, boo
     a.mode = pl->n_s == 3 ? 0 : 1;
     a.z = z;
     a.mask = mask;
-    return launch<float>(a, pl->fft32.logm, pl->fft32.n_tiles, pl->stream);
+    return launch<float>(a, pl->fft32, pl->stream);
 }
 
 int toeplitz_map32_layers(mm_plan_t pl, const double* x, int64_t x_step, const float* xp,
@@ -1388,7 +1679,7 @@ int toeplitz_map32_layers(mm_plan_t pl, const double* x, int64_t x_step, const f
     a.xp_step = xp_step;
     a.z_step = z_step;
     a.on_step = on_step;
-    return launch<float>(a, pl->fft32.logm, pl->fft32.n_tiles, pl->stream);
+    return launch<float>(a, pl->fft32, pl->stream);
 }
 
 int toeplitz_tod64(mm_plan_t pl, const void* y, int y_f64, double* z) {
@@ -1397,7 +1688,7 @@ int toeplitz_tod64(mm_plan_t pl, const void* y, int y_f64, double* z) {
     a.y_f64 = y_f64;
     a.mode = y_f64 ? 2 : 3;
     a.z = z;
-    return launch<double>(a, pl->fft64.logm, pl->fft64.n_tiles, pl->stream);
+    return launch<double>(a, pl->fft64, pl->stream);
 }
 
 int toeplitz_tod32(mm_plan_t pl, const void* y, int y_f64, float* z) {
@@ -1406,7 +1697,7 @@ int toeplitz_tod32(mm_plan_t pl, const void* y, int y_f64, float* z) {
     a.y_f64 = y_f64;
     a.mode = y_f64 ? 2 : 3;
     a.z = z;
-    return launch<float>(a, pl->fft32.logm, pl->fft32.n_tiles, pl->stream);
+    return launch<float>(a, pl->fft32, pl->stream);
 }
 
 // ------------------------------------------------------------------ FFT length autotuner
@@ -1422,6 +1713,7 @@ void swap_tiling(FftTiling& a, FftTiling& b) {
     std::swap(a.logm, b.logm);
     std::swap(a.n_r, b.n_r);
     std::swap(a.n_tiles, b.n_tiles);
+    std::swap(a.paired, b.paired);
     a.tile_out.swap(b.tile_out);
     a.tile_len.swap(b.tile_len);
     a.tile_int.swap(b.tile_int);
@@ -1444,10 +1736,10 @@ int time_map_launch(mm_plan_t pl, FftTiling& ft, T* xp, const double* x, T* z, f
     hipEvent_t e0, e1;
     MM_HIP(hipEventCreate(&e0));
     MM_HIP(hipEventCreate(&e1));
-    int s = launch<T>(a, ft.logm, ft.n_tiles, pl->stream);  // warm-up
+    int s = launch<T>(a, ft, pl->stream);  // warm-up
     if (s == MM_OK) {
         (void)hipEventRecord(e0, pl->stream);
-        for (int r = 0; r < 3 && s == MM_OK; ++r) s = launch<T>(a, ft.logm, ft.n_tiles, pl->stream);
+        for (int r = 0; r < 3 && s == MM_OK; ++r) s = launch<T>(a, ft, pl->stream);
         (void)hipEventRecord(e1, pl->stream);
         (void)hipEventSynchronize(e1);
         (void)hipEventElapsedTime(ms, e0, e1);

@@ -127,3 +127,51 @@ def test_taps_of_any_interval_length(lam, lens):
         assert (np.abs(dt[j, :, :K + 1] - D).max(1) <= 2 * unit * big).all(), (lam, n)
         assert not dt[j, :, K + 1:].any()
     plan.close()
+
+
+@pytest.mark.parametrize("n_r,lam", [(4096, 900), (4096, 1536), (8192, 2048), (8192, 3072)])
+def test_paired_tiles_at_their_edges(n_r, lam):
+    """FP64 N^-1 and A x at the lengths whose tiles go in pairs: intervals of one tile, of an
+    empty or one-sample second tile, of exactly full and of odd numbers of tiles, against the
+    oracle's banded sums; a sample that is not finite stays within its own window's outputs and
+    its own interval."""
+    lmax = n_r - 2 * lam
+    lens = [1, 2, 3, lmax - 1, lmax, lmax + 1, 2 * lmax - 1, 2 * lmax, 2 * lmax + 1, 3 * lmax + 5]
+    off = np.concatenate([[0], np.cumsum(lens)])
+    n, k = int(off[-1]), len(lens)
+    r = np.random.default_rng(n_r + lam)
+    psd = np.stack([r.uniform(0.5, 2.0, k), r.uniform(1.0, 2.0, k), r.uniform(1.0, 2.0, k)], 1)
+    n_pix = 200
+    pix = r.integers(0, n_pix, n).astype(np.int32)
+    ang = r.uniform(0, np.pi, n)
+    w = np.stack([np.cos(2 * ang), np.sin(2 * ang)], 1)
+    plan = Plan(torch.from_numpy(pix).cuda(), torch.from_numpy(w).cuda(), n_pix, off, psd,
+                n_stokes=3, lam=lam, rcond_min=0.0, fft_len_f64=n_r)
+    assert plan.fft_lengths()[0] == n_r
+    taps = [O.toeplitz_taps(m, *p, lam, 200.0) for m, p in zip(lens, psd)]
+    y = r.standard_normal(n)
+    ref = O.toeplitz_apply(y, off, taps)
+    z = plan.apply_Ninv(torch.from_numpy(y).cuda()).cpu().numpy()
+    assert np.abs(z - ref).max() <= 1e-12 * np.abs(ref).max()
+    # map mode
+    x = r.standard_normal(plan.n_vec)
+    m = x.reshape(-1, 3)[np.searchsorted(np.unique(pix), pix)]
+    za = O.toeplitz_apply(m[:, 0] + w[:, 0] * m[:, 1] + w[:, 1] * m[:, 2], off, taps)
+    cid = np.searchsorted(np.unique(pix), pix)
+    ax = np.stack([np.bincount(cid, za * c) for c in (np.ones(n), w[:, 0], w[:, 1])], 1).reshape(-1)
+    got = plan.apply_A(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.abs(got - ax).max() <= 1e-12 * np.abs(ax).max()
+    # one infinite sample in the middle of the first tile of the last interval
+    bad = y.copy()
+    t = int(off[-2]) + (lens[-1] + 3) // 4 // 2
+    bad[t] = np.inf
+    zb = plan.apply_Ninv(torch.from_numpy(bad).cuda()).cpu().numpy()
+    tile = -(-lens[-1] // 4)
+    clean = np.ones(n, bool)
+    for a in range(int(off[-2]), n, tile):  # the tiles whose windows hold the sample
+        if a - lam <= t < min(a + tile, n) + lam:
+            clean[a:a + tile] = False
+    assert np.array_equal(zb[:off[-2]], z[:off[-2]])
+    assert not np.isfinite(zb[t])
+    assert np.abs(zb - ref)[clean].max() <= 1e-12 * np.abs(ref).max()
+    plan.close()
