@@ -377,7 +377,8 @@ int mm_gemm_tn_f64_noalloc(void* stream, const double* A, const double* B, int64
  * hot-path kernels (for measurements; off by default).  enable = 1 starts a fresh window,
  * 0 stops recording.  Kernel ids: MM_K_NINV32 / MM_K_NINV64 (overlap-save N^-1 with the
  * de-pointing gather fused, FP32 / FP64), MM_K_PT32 / MM_K_PT64 (P^T segmented reduction),
- * MM_K_PRECOND (block-Jacobi or two-level application), MM_K_VEC (CG vector updates).
+ * MM_K_PRECOND (two-level application; with block Jacobi the x, r update it is fused with),
+ * MM_K_VEC (the other CG vector updates).
  * mm_profile_read synchronises the stream and returns the number of launches and their
  * summed duration in ms. */
 enum { MM_K_NINV32 = 0, MM_K_NINV64 = 1, MM_K_PT32 = 2, MM_K_PT64 = 3, MM_K_PRECOND = 4,

@@ -194,8 +194,8 @@ void prof_invalidate(mm_plan_t pl, const size_t* mark, int first_skipped) {
             if (pl->prof_ev[k][i].tag >= first_skipped) pl->prof_ev[k][i].valid = false;
 }
 
+// y = A x of the map whose packed form is already in xp64 / xp32
 static int apply_A64_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag) {
-    MM_TRY(pack_map64(pl, x));
     MM_TRY(prof_begin(pl, MM_K_NINV64, tag));
     MM_TRY(toeplitz_map64(pl, x, pl->tod64a.p, mask));
     MM_TRY(prof_end(pl, MM_K_NINV64));
@@ -205,7 +205,6 @@ static int apply_A64_tag(mm_plan_t pl, const double* x, double* y, const int* ma
 }
 
 static int apply_A32_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag) {
-    MM_TRY(pack_map32(pl, x));
     MM_TRY(prof_begin(pl, MM_K_NINV32, tag));
     MM_TRY(toeplitz_map32(pl, x, pl->tod32a.p, mask));
     MM_TRY(prof_end(pl, MM_K_NINV32));
@@ -215,6 +214,7 @@ static int apply_A32_tag(mm_plan_t pl, const double* x, double* y, const int* ma
 }
 
 int apply_A64(mm_plan_t pl, const double* x, double* y, const int* mask) {
+    MM_TRY(pack_map64(pl, x));
     return apply_A64_tag(pl, x, y, mask, -1);
 }
 
@@ -236,6 +236,7 @@ int apply_A32_sparse(mm_plan_t pl, const double* x, double* y, const uint8_t* in
 }
 
 int apply_A32(mm_plan_t pl, const double* x, double* y, const int* mask) {
+    MM_TRY(pack_map32(pl, x));
     return apply_A32_tag(pl, x, y, mask, -1);
 }
 
@@ -306,21 +307,6 @@ int prob_sq_norms(mm_plan_t pl, const double* v, std::vector<double>& out) {
     return MM_OK;
 }
 
-// One PCG iteration for every iterating problem (mask act): q = A p, alpha, x and r,
-// convergence test, z = M r, beta and p.  Launch arguments do not change between
-// iterations, so the sequence can be captured once and replayed.
-int pcg_iteration(mm_plan_t pl, bool op32, double* x, double* r, double* p, double* q,
-                  int tag) {
-    PcgCtl c = batch_ctl(pl);
-    c.mask = pl->act.p;
-    MM_TRY(op32 ? apply_A32_tag(pl, p, q, c.mask, tag) : apply_A64_tag(pl, p, q, c.mask, tag));
-    MM_TRY(prof_begin(pl, MM_K_VEC, tag));
-    MM_TRY(vec_dot(pl, p, q, kSlotPQ, c));
-    MM_TRY(pcg_update_xr(pl, x, r, p, q, c));
-    MM_TRY(prof_end(pl, MM_K_VEC));
-    return MM_OK;
-}
-
 struct EngineArgs {
     int pc = MM_BJ;
     bool op32 = false;
@@ -331,25 +317,32 @@ struct EngineArgs {
     double replace_ratio = 0.0;
 };
 
-// the part of an iteration after the x, r update
-int pcg_iteration_tail(mm_plan_t pl, const EngineArgs& ea, double* r, double* z, double* p,
-                       int tag) {
+// One PCG iteration for every iterating problem (mask act): q = A p (p's packed map was
+// written with p), alpha, x and r, z = M r, convergence test, beta and p.  Launch arguments
+// do not change between iterations, so the sequence can be captured once and replayed.
+int full_iteration(mm_plan_t pl, const EngineArgs& ea, double* x, double* r, double* z, double* p,
+                   double* q, int tag) {
     PcgCtl c = batch_ctl(pl);
     c.mask = pl->act.p;
     c.replace = ea.replace;
     c.replace_ratio = ea.replace_ratio;
     c.max_iter = ea.max_iter;
-    MM_TRY(pcg_check(pl, c, 0));
-    MM_TRY(precond(pl, ea.pc, r, z, c, tag));
+    MM_TRY(ea.op32 ? apply_A32_tag(pl, p, q, c.mask, tag) : apply_A64_tag(pl, p, q, c.mask, tag));
     MM_TRY(prof_begin(pl, MM_K_VEC, tag));
-    MM_TRY(pcg_update_p(pl, p, z, c));
+    MM_TRY(vec_dot(pl, p, q, kSlotPQ, c));
+    if (ea.pc == MM_BJ) {
+        MM_TRY(prof_end(pl, MM_K_VEC));
+        MM_TRY(prof_begin(pl, MM_K_PRECOND, tag));
+        MM_TRY(pcg_update_xr_bj(pl, x, r, z, p, q, c));
+        MM_TRY(prof_end(pl, MM_K_PRECOND));
+    } else {
+        MM_TRY(pcg_update_xr(pl, x, r, p, q, c));
+        MM_TRY(prof_end(pl, MM_K_VEC));
+        MM_TRY(precond(pl, ea.pc, r, z, c, tag));
+    }
+    MM_TRY(prof_begin(pl, MM_K_VEC, tag));
+    MM_TRY(pcg_update_p(pl, p, z, ea.op32, 1, c));
     return prof_end(pl, MM_K_VEC);
-}
-
-int full_iteration(mm_plan_t pl, const EngineArgs& ea, double* x, double* r, double* z, double* p,
-                   double* q, int tag) {
-    MM_TRY(pcg_iteration(pl, ea.op32, x, r, p, q, tag));
-    return pcg_iteration_tail(pl, ea, r, z, p, tag);
 }
 
 // PCG on A x_b = b_b for every problem b of the plan, from x (or x = 0 when x_zero).
@@ -398,10 +391,10 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
     PcgCtl ca = all;
     ca.mask = pl->act.p;
     MM_TRY(vec_dot(pl, r, r, kSlotRR, ca));
-    MM_TRY(pcg_check(pl, ca, 1));
+    MM_TRY(pcg_check(pl, ca));
     MM_TRY(precond(pl, ea.pc, r, z, ca));
     ca.first = 1;
-    MM_TRY(pcg_update_p(pl, p, z, ca));
+    MM_TRY(pcg_update_p(pl, p, z, ea.op32, 0, ca));
     MM_TRY(read_scalars(pl));
     auto count = [&](int state) {
         int k = 0;
@@ -473,7 +466,9 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
             // A-DEF2: the replaced residual gets the coarse correction again (Z^T r = 0)
             if (ea.pc == MM_ADEF2) MM_TRY(coarse_start(pl, xw, r, pl->sel.p));
             MM_TRY(precond(pl, ea.pc, r, z, cs));
-            MM_TRY(pcg_update_p(pl, p, z, cs));
+            MM_TRY(pcg_update_p(pl, p, z, ea.op32, 0, cs));
+            // the evaluation packed x where the FP64 iteration keeps its packed p
+            if (!ea.op32) MM_TRY(pack_map64(pl, p));
             MM_TRY(pcg_resume(pl, all));
             MM_TRY(read_scalars(pl));
         }

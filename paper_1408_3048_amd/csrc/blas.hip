@@ -29,7 +29,33 @@ __global__ __launch_bounds__(kVecThreads) void k_dot(const double* __restrict__ 
     write_partial_at(acc, slot_part(c, slot, v.b), v.k, red);
 }
 
-// alpha = r^T z / p^T q; x += alpha p; r -= alpha q; partials of ||r||^2
+// the step length alpha = r^T z / p^T q of a block's problem from the partials of p^T q, and
+// its bookkeeping; false (for every thread) on a breakdown.  All threads must call.
+__device__ __forceinline__ bool step_length(const PcgCtl& c, const VecBlock& v, double* red,
+                                            double& alpha) {
+    PcgScalars& s = c.sc[v.b];
+    const double pq = reduce_partials(slot_part(c, kSlotPQ, v.b), kVecBlocks, red);
+    const double rz = c.rz_hist[(int64_t)v.b * c.hstride + s.iter];
+    if (!(pq > 0.0 && isfinite(pq) && isfinite(rz))) {
+        if (first_thread(v)) {
+            s.status = 1;
+            s.state = kBreakdown;
+            s.pq = pq;
+            c.act[v.b] = 0;
+        }
+        return false;
+    }
+    alpha = rz / pq;
+    if (first_thread(v)) {
+        s.alpha = alpha;
+        s.pq = pq;
+        s.iter_next = s.iter + 1;
+        if (c.alpha_hist) c.alpha_hist[(int64_t)v.b * c.hstride + s.iter] = alpha;
+    }
+    return true;
+}
+
+// x += alpha p; r -= alpha q; partials of ||r||^2
 __global__ __launch_bounds__(kVecThreads) void k_update_xr(double* __restrict__ x,
                                                            double* __restrict__ r,
                                                            const double* __restrict__ p,
@@ -38,26 +64,8 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(double* __restrict__ 
     __shared__ double red[kVecThreads];
     const VecBlock v = vec_block(c, ns, true);
     if (c.mask && !c.mask[v.b]) return;
-    PcgScalars& s = c.sc[v.b];
-    const double pq = reduce_partials(slot_part(c, kSlotPQ, v.b), kVecBlocks, red);
-    const double rz = c.rz_hist[(int64_t)v.b * c.hstride + s.iter];
-    const bool ok = pq > 0.0 && isfinite(pq) && isfinite(rz);
-    if (!ok) {
-        if (first_thread(v)) {
-            s.status = 1;
-            s.state = kBreakdown;
-            s.pq = pq;
-            c.act[v.b] = 0;
-        }
-        return;
-    }
-    const double alpha = rz / pq;
-    if (first_thread(v)) {
-        s.alpha = alpha;
-        s.pq = pq;
-        s.iter_next = s.iter + 1;
-        if (c.alpha_hist) c.alpha_hist[(int64_t)v.b * c.hstride + s.iter] = alpha;
-    }
+    double alpha;
+    if (!step_length(c, v, red, alpha)) return;
     double acc = 0.0;
     for (int64_t i = (int64_t)v.k * kVecThreads + threadIdx.x; i < v.n;
          i += v.stride) {
@@ -70,19 +78,87 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(double* __restrict__ 
     write_partial_at(acc, slot_part(c, kSlotRR, v.b), v.k, red);
 }
 
-// beta = r_new^T z_new / r^T z; p = z + beta p (p = z on the first call).  The
-// iteration count it = iter is that of the iteration just completed (or of the last
-// completed one when resuming after a residual evaluation): r^T z of the new residual
-// is stored at rz_hist[it] and divided by rz_hist[it - 1].
+// k_update_xr and block Jacobi in one pass per pixel: z = M_BD r of the new residual while it
+// is in registers, partials of ||r||^2 and r^T z.  One launch and one read of r instead of
+// three launches with k_pcg_check between them (each about 2.5-4.5 us when small)
+template <int NS>
+__global__ __launch_bounds__(kVecThreads) void k_update_xr_bj(
+    double* __restrict__ x, double* __restrict__ r, double* __restrict__ z,
+    const double* __restrict__ p, const double* __restrict__ q, const double* __restrict__ bj,
+    PcgCtl c) {
+    __shared__ double red[kVecThreads];
+    const VecBlock v = vec_block(c, NS, false);
+    if (c.mask && !c.mask[v.b]) return;
+    double alpha;
+    if (!step_length(c, v, red, alpha)) return;
+    double rr = 0.0, rz = 0.0;
+    for (int64_t i = (int64_t)v.k * kVecThreads + threadIdx.x; i < v.n; i += v.stride) {
+        const int64_t px = v.base + i, e = px * NS;
+        double rv[NS], zv[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            x[e + s] += alpha * p[e + s];
+            rv[s] = r[e + s] - alpha * q[e + s];
+            r[e + s] = rv[s];
+            rr += rv[s] * rv[s];
+        }
+        bj_block<NS>(bj + (NS == 3 ? 6 : 1) * px, rv, zv);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            z[e + s] = zv[s];
+            rz += rv[s] * zv[s];
+        }
+    }
+    write_partial_at(rr, slot_part(c, kSlotRR, v.b), v.k, red);
+    write_partial_at(rz, slot_part(c, kSlotRZ, v.b), v.k, red);
+}
+
+// The convergence test of problem b on its recursive residual (partials of ||r||^2): after an
+// iteration (initial = 0) it also counts the iteration and records the history.  Returns the
+// problem's new state; thread 0 writes it where `write` is set.  All threads must call.
+__device__ __forceinline__ int test_residual(const PcgCtl& c, int b, int initial, bool write,
+                                             double* red) {
+    const double rr = reduce_partials(slot_part(c, kSlotRR, b), kVecBlocks, red);
+    PcgScalars& s = c.sc[b];
+    const int iter = initial ? s.iter : s.iter_next;
+    const double rel = sqrt(rr) / s.bnorm;
+    int st = kActive;
+    if (rel <= s.tol) st = (!initial && c.replace) ? kCheck : kDone;
+    else if (!initial && c.replace_ratio > 0.0 && rel < c.replace_ratio * s.last_rel) st = kCheck;
+    else if (!initial && iter >= c.max_iter) st = kMaxIter;
+    if (write && threadIdx.x == 0) {
+        s.iter = iter;
+        s.rr = rr;
+        s.rel = rel;
+        if (!initial && c.hist) c.hist[(int64_t)b * c.hstride + iter - 1] = rel;
+        if (st != kActive) {
+            s.state = st;
+            c.act[b] = 0;
+        }
+    }
+    return st;
+}
+
+// beta = r_new^T z_new / r^T z; p = z + beta p (p = z on the first call), and p's packed map
+// xp for the next A p.  The iteration count it = iter_next is that of the iteration just
+// completed (or of the last completed one when resuming after a residual evaluation): r^T z
+// of the new residual is stored at rz_hist[it] and divided by rz_hist[it - 1].
+// test: the launch first takes the iteration's convergence test; every block of a problem
+// takes it from the same partials, its first block writes the outcome (the others read
+// neither iter nor state, and where it clears act, none has anything left to do).
+// The test and the packing were launches of their own (2.5-4.6 and 1.4-4.7 us each)
+template <int NS, typename TP>
 __global__ __launch_bounds__(kVecThreads) void k_update_p(double* __restrict__ p,
-                                                          const double* __restrict__ z, int ns,
+                                                          const double* __restrict__ z,
+                                                          TP* __restrict__ xp, int test,
                                                           PcgCtl c) {
     __shared__ double red[kVecThreads];
-    const VecBlock v = vec_block(c, ns, true);
+    const VecBlock v = vec_block(c, NS, false);
     if (c.mask && !c.mask[v.b]) return;
     PcgScalars& s = c.sc[v.b];
+    const int it = s.iter_next;
+    if (test && test_residual(c, v.b, 0, v.k == 0, red) != kActive) return;
     const double rz_new = reduce_partials(slot_part(c, kSlotRZ, v.b), kVecBlocks, red);
-    const int it = s.iter;
     double* rh = c.rz_hist + (int64_t)v.b * c.hstride;
     const double beta = c.first ? 0.0 : rz_new / rh[it - 1];
     if (first_thread(v)) {
@@ -92,12 +168,22 @@ __global__ __launch_bounds__(kVecThreads) void k_update_p(double* __restrict__ p
     // Krylov recording: z of this iteration (rewritten when a residual evaluation resumes
     // the same iteration, together with rz_hist[it])
     double* kz = c.krylov && it < c.kcap ? c.krylov + (int64_t)it * c.knv : nullptr;
-    for (int64_t i = (int64_t)v.k * kVecThreads + threadIdx.x; i < v.n;
-         i += v.stride) {
-        const int64_t e = v.base + i;
-        const double zv = z[e];
-        p[e] = c.first ? zv : zv + beta * p[e];
-        if (kz) kz[e] = zv;
+    for (int64_t i = (int64_t)v.k * kVecThreads + threadIdx.x; i < v.n; i += v.stride) {
+        const int64_t px = v.base + i, e = px * NS;
+        double pv[NS];
+#pragma unroll
+        for (int s1 = 0; s1 < NS; ++s1) {
+            const double zv = z[e + s1];
+            pv[s1] = c.first ? zv : zv + beta * p[e + s1];
+            p[e + s1] = pv[s1];
+            if (kz) kz[e + s1] = zv;
+        }
+        if constexpr (NS == 3) {
+            xp[4 * px] = (TP)pv[0];
+            xp[4 * px + 1] = (TP)pv[1];
+            xp[4 * px + 2] = (TP)pv[2];
+            xp[4 * px + 3] = (TP)0;
+        }
     }
 }
 
@@ -167,28 +253,12 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_init(PcgCtl c, double tol, 
     }
 }
 
-// convergence test on the recursive residual (RR partials) of every iterating problem;
-// after an iteration (initial = 0) it also counts the iteration and records the history
-__global__ __launch_bounds__(kVecThreads) void k_pcg_check(PcgCtl c, int initial) {
+// convergence test of the initial residual (RR partials) of every iterating problem
+__global__ __launch_bounds__(kVecThreads) void k_pcg_check(PcgCtl c) {
     __shared__ double red[kVecThreads];
     const int b = blockIdx.x;
     if (!c.act[b]) return;
-    const double rr = reduce_partials(slot_part(c, kSlotRR, b), kVecBlocks, red);
-    if (threadIdx.x != 0) return;
-    PcgScalars& s = c.sc[b];
-    if (!initial) s.iter = s.iter_next;
-    const double rel = sqrt(rr) / s.bnorm;
-    s.rr = rr;
-    s.rel = rel;
-    if (!initial && c.hist) c.hist[(int64_t)b * c.hstride + s.iter - 1] = rel;
-    int st = kActive;
-    if (rel <= s.tol) st = (!initial && c.replace) ? kCheck : kDone;
-    else if (!initial && c.replace_ratio > 0.0 && rel < c.replace_ratio * s.last_rel) st = kCheck;
-    else if (!initial && s.iter >= c.max_iter) st = kMaxIter;
-    if (st != kActive) {
-        s.state = st;
-        c.act[b] = 0;
-    }
+    test_residual(c, b, 1, true, red);
 }
 
 // after b - A x of the problems in c.mask (state kCheck) is in r with its Aux partials:
@@ -317,9 +387,31 @@ int pcg_update_xr(mm_plan_t pl, double* x, double* r, const double* p, const dou
     return MM_OK;
 }
 
-int pcg_update_p(mm_plan_t pl, double* p, const double* z, const PcgCtl& ctl) {
-    hipLaunchKernelGGL(k_update_p, dim3(pl->n_eblk), dim3(kVecThreads), 0, pl->stream, p, z,
-                       pl->n_s, ctl);
+int pcg_update_xr_bj(mm_plan_t pl, double* x, double* r, double* z, const double* p,
+                     const double* q, const PcgCtl& ctl) {
+    const dim3 g(pl->n_pblk), t(kVecThreads);
+    if (pl->n_s == 3)
+        hipLaunchKernelGGL(k_update_xr_bj<3>, g, t, 0, pl->stream, x, r, z, p, q,
+                           (const double*)pl->bj.p, ctl);
+    else
+        hipLaunchKernelGGL(k_update_xr_bj<1>, g, t, 0, pl->stream, x, r, z, p, q,
+                           (const double*)pl->bj.p, ctl);
+    MM_HIP(hipGetLastError());
+    return MM_OK;
+}
+
+int pcg_update_p(mm_plan_t pl, double* p, const double* z, bool op32, int test,
+                 const PcgCtl& ctl) {
+    const dim3 g(pl->n_pblk), t(kVecThreads);
+    if (pl->n_s != 3)
+        hipLaunchKernelGGL((k_update_p<1, double>), g, t, 0, pl->stream, p, z, (double*)nullptr,
+                           test, ctl);
+    else if (op32)
+        hipLaunchKernelGGL((k_update_p<3, float>), g, t, 0, pl->stream, p, z, pl->xp32.p, test,
+                           ctl);
+    else
+        hipLaunchKernelGGL((k_update_p<3, double>), g, t, 0, pl->stream, p, z, pl->xp64.p, test,
+                           ctl);
     MM_HIP(hipGetLastError());
     return MM_OK;
 }
@@ -353,9 +445,8 @@ int pcg_init(mm_plan_t pl, const PcgCtl& ctl, double tol, int zero_b_done) {
     return MM_OK;
 }
 
-int pcg_check(mm_plan_t pl, const PcgCtl& ctl, int initial) {
-    hipLaunchKernelGGL(k_pcg_check, dim3(pl->n_prob), dim3(kVecThreads), 0, pl->stream, ctl,
-                       initial);
+int pcg_check(mm_plan_t pl, const PcgCtl& ctl) {
+    hipLaunchKernelGGL(k_pcg_check, dim3(pl->n_prob), dim3(kVecThreads), 0, pl->stream, ctl);
     MM_HIP(hipGetLastError());
     return MM_OK;
 }

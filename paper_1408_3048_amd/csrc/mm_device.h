@@ -89,4 +89,17 @@ __device__ __forceinline__ VecBlock vec_block(const PcgCtl& c, int ns, bool elem
     return v;
 }
 
+// z = M_BD r of one pixel: its block bj (6 entries of the symmetric inverse, or 1)
+template <int NS>
+__device__ __forceinline__ void bj_block(const double* __restrict__ bj, const double* r,
+                                         double* z) {
+    if constexpr (NS == 1) {
+        z[0] = bj[0] * r[0];
+    } else {
+        z[0] = bj[0] * r[0] + bj[1] * r[1] + bj[2] * r[2];
+        z[1] = bj[1] * r[0] + bj[3] * r[1] + bj[4] * r[2];
+        z[2] = bj[2] * r[0] + bj[4] * r[1] + bj[5] * r[2];
+    }
+}
+
 }  // namespace mm

@@ -439,14 +439,20 @@ PcgCtl batch_ctl(mm_plan_t pl);
 int vec_dot(mm_plan_t pl, const double* a, const double* b, int slot, const PcgCtl& ctl);
 int pcg_update_xr(mm_plan_t pl, double* x, double* r, const double* p, const double* q,
                   const PcgCtl& ctl);
-int pcg_update_p(mm_plan_t pl, double* p, const double* z, const PcgCtl& ctl);
+// the x, r update followed by z = M_BD r, with partials of ||r||^2 and r^T z
+int pcg_update_xr_bj(mm_plan_t pl, double* x, double* r, double* z, const double* p,
+                     const double* q, const PcgCtl& ctl);
+// p = z + beta p and its packed map (xp32 with op32, else xp64); test: after the iteration's
+// convergence test
+int pcg_update_p(mm_plan_t pl, double* p, const double* z, bool op32, int test,
+                 const PcgCtl& ctl);
 // out = b - y for masked problems, with partials of ||out||^2 in the Aux slot
 int vec_residual(mm_plan_t pl, const double* b, const double* y, double* out, const PcgCtl& ctl);
 int vec_axpby(mm_plan_t pl, double a, const double* x, double b, const double* y, double* out);
 int vec_zero_flagged(mm_plan_t pl, double* x, const int* flag, const PcgCtl& ctl);
 // control kernels (one block per problem)
 int pcg_init(mm_plan_t pl, const PcgCtl& ctl, double tol, int zero_b_done);
-int pcg_check(mm_plan_t pl, const PcgCtl& ctl, int initial);
+int pcg_check(mm_plan_t pl, const PcgCtl& ctl);  // of the initial residual
 int pcg_decide(mm_plan_t pl, const PcgCtl& ctl);
 int pcg_select(mm_plan_t pl, const PcgCtl& ctl);
 int pcg_resume(mm_plan_t pl, const PcgCtl& ctl);

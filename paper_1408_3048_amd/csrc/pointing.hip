@@ -530,21 +530,14 @@ __global__ __launch_bounds__(kVecThreads) void k_bj_apply(const double* __restri
     for (int64_t q = (int64_t)vb.k * kVecThreads + threadIdx.x; q < vb.n;
          q += vb.stride) {
         const int64_t c = vb.base + q;
-        if constexpr (NS == 1) {
-            const double rv = r[c];
-            const double zv = bj[c] * rv;
-            z[c] = zv;
-            acc += rv * zv;
-        } else {
-            const double* m = bj + 6 * c;
-            const double r0 = r[3 * c], r1 = r[3 * c + 1], r2 = r[3 * c + 2];
-            const double z0 = m[0] * r0 + m[1] * r1 + m[2] * r2;
-            const double z1 = m[1] * r0 + m[3] * r1 + m[4] * r2;
-            const double z2 = m[2] * r0 + m[4] * r1 + m[5] * r2;
-            z[3 * c] = z0;
-            z[3 * c + 1] = z1;
-            z[3 * c + 2] = z2;
-            acc += r0 * z0 + r1 * z1 + r2 * z2;
+        double rv[NS], zv[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) rv[s] = r[NS * c + s];
+        bj_block<NS>(bj + (NS == 3 ? 6 : 1) * c, rv, zv);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            z[NS * c + s] = zv[s];
+            acc += rv[s] * zv[s];
         }
     }
     if (ctl.part) write_partial_at(acc, slot_part(ctl, kSlotRZ, vb.b), vb.k, red);

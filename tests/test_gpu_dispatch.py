@@ -175,3 +175,35 @@ def test_paired_tiles_at_their_edges(n_r, lam):
     assert not np.isfinite(zb[t])
     assert np.abs(zb - ref)[clean].max() <= 1e-12 * np.abs(ref).max()
     plan.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("side", [7, 16, 23])
+def test_fused_pcg_updates_over_a_batch(side, precision):
+    """The fused update, preconditioning, convergence-test and packing launches for problems of
+    49 to 1058 pixels (around the vector kernels' blocks of 256) that stop at different
+    iterations: the evaluation of one problem's true residual leaves the others' search
+    directions (and their packed maps) alone.  Each problem equals its standalone solve bit for
+    bit, iteration by iteration, and solves its system."""
+    kw = dict(n_det=4, lam=64, fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+    scans = [synth.raster_iqu(side=s, spp=8, interval_len=s * s * 4, seed_key=80 + s, **kw)
+             for s in (side, 2 * side, side + 1 + side % 2)]
+    opts = dict(precision="mixed", fft_len_f64=4096, fft_len_f32=4096)
+    pb = _gpu_plan(scans, **opts)
+    off = pb.problem_pixels() * 3
+    d = torch.from_numpy(np.concatenate([sc.noise for sc in scans])).cuda()
+    xb, ib = pb.pcg_solve(pb.rhs(d), precision=precision, tol=1e-9, max_iter=3000)
+    assert len({p["iterations"] for p in ib["problems"]}) > 1
+    for b, sc in enumerate(scans):
+        p1 = Plan.from_scan(sc, **opts)
+        rhs = p1.rhs(torch.from_numpy(sc.noise).cuda())
+        x1, i1 = p1.pcg_solve(rhs, precision=precision, tol=1e-9, max_iter=3000)
+        assert torch.equal(x1, xb[off[b]:off[b + 1]]), b
+        assert i1["iterations"] == ib["problems"][b]["iterations"]
+        assert np.array_equal(i1["history"], ib["problems"][b]["history"])
+        pr = O.Problem.from_scan(sc)
+        bn = rhs.cpu().numpy()
+        res = np.linalg.norm(bn - pr.apply_A(x1.cpu().numpy())) / np.linalg.norm(bn)
+        assert res <= 1.01e-9, (b, res)
+        p1.close()
+    pb.close()
