@@ -279,7 +279,7 @@ def batched_leg(tol, warmup=1, graph=True):
                    iterations_max=max(its), iterations_mean=float(np.mean(its)),
                    rel_residual_max=info["rel_residual_max"], r_eff=plan.coarse_rank(),
                    method="mixed two-level PCG, one batched plan, " +
-                   ("graph-captured iterations" if graph else "launches issued one by one"))
+                   ("graph option on" if graph else "graph option off"))
         log(f"batched {'warmup' if i < warmup else 'timed'}: {tt * 1e3:.1f} ms {res}")
         plan.close()
         # the outputs are consumed here, so the next iteration's allocations reuse them
@@ -618,8 +618,8 @@ def main():
                     help="only run the 256-problem batched leg (profiling runs) and print its "
                          "record")
     ap.add_argument("--graph", type=int, default=1,
-                    help="batched leg: 1 captures the PCG iterations in HIP graphs, 0 issues "
-                         "every launch from the host (kernel traces of the iterations)")
+                    help="batched leg: the plan's graph option (0: every launch from the host on "
+                         "the caller's stream, also in small plans)")
     ap.add_argument("--ring-only", action="store_true",
                     help="only run the ring-scan share leg (profiling runs) and print its record")
     args = ap.parse_args()

@@ -250,6 +250,8 @@ void drop_graphs(mm_plan_t pl) {
                 (void)hipGraphExecDestroy(g);
                 g = nullptr;
             }
+    for (auto& row : pl->gkey)
+        for (auto& k : row) k = mm_plan_s::GraphKey();
 }
 
 namespace {
@@ -261,6 +263,8 @@ using clk = std::chrono::steady_clock;
 constexpr double kReplaceRatio = 1e-4;
 // iterations launched between two reads of the problem states
 constexpr int kChunk = 4;
+// samples from which launches issued one by one are as fast as replayed ones
+constexpr int64_t kGraphMaxSamples = int64_t(1) << 18;
 
 double ms_since(clk::time_point t0) {
     return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
@@ -402,19 +406,30 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
         return k;
     };
     // graph of one chunk of kChunk iterations for this operator / preconditioner and control
-    // arguments (one launch per chunk: the gaps between graph launches are paid once)
+    // arguments (one launch per chunk: the gaps between graph launches are paid once).
+    // Capture and instantiation take 110-370 us and the replays of small problems save 24 us a
+    // solve (27 iterations, 2^14 samples: 1097 us against 1121), so they come with the second
+    // solve that a plan does with the same arguments.  From kGraphMaxSamples on launches issued
+    // one by one are as fast or faster: 2^18 samples 1590 us both ways, 2^22 FP64 two-level
+    // 6470 replayed against 6350, 2^24 mixed two-level 15820 against 15690, 48 problems of
+    // 150000 samples 6990 against 6790.
     const bool use_graph = pl->opts.graph != 0 && !pl->prof_on && pl->gstream != nullptr &&
-                           pl->stream == pl->gstream;
+                           pl->stream == pl->gstream && pl->n_t < kGraphMaxSamples;
     const int gi = ea.op32 ? 1 : 0, gj = ea.pc;
     hipGraphExec_t& gx = pl->gexec[gi][gj];
     auto& key = pl->gkey[gi][gj];
-    if (use_graph && gx &&
-        (key.replace != (int)ea.replace || key.ratio != ea.replace_ratio ||
-         key.max_iter != ea.max_iter)) {
+    const bool again = use_graph && key.replace == (int)ea.replace &&
+                       key.ratio == ea.replace_ratio && key.max_iter == ea.max_iter;
+    if (use_graph && gx && !again) {
         (void)hipGraphExecDestroy(gx);
         gx = nullptr;
     }
-    if (use_graph && !gx) {
+    if (use_graph) {
+        key.replace = (int)ea.replace;
+        key.ratio = ea.replace_ratio;
+        key.max_iter = ea.max_iter;
+    }
+    if (again && !gx) {
         hipGraph_t g = nullptr;
         MM_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
         int s1 = MM_OK;
@@ -430,9 +445,6 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
         (void)hipGraphDestroy(g);
         if (e2 != hipSuccess) gx = nullptr;
         MM_HIP(e2);
-        key.replace = (int)ea.replace;
-        key.ratio = ea.replace_ratio;
-        key.max_iter = ea.max_iter;
     }
     const bool graph_ok = use_graph && gx;
     int host_it = 0;

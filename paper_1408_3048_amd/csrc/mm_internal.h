@@ -302,7 +302,7 @@ struct mm_plan_s {
     // MM_ADEF2)
     hipStream_t gstream = nullptr;      // non-blocking stream the graphs are captured on
     hipGraphExec_t gexec[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
-    struct GraphKey {          // control arguments baked into a captured iteration
+    struct GraphKey {          // control arguments of the last solve, baked into its graph
         int replace = -1;
         double ratio = 0.0;
         int max_iter = 0;

@@ -207,3 +207,31 @@ def test_fused_pcg_updates_over_a_batch(side, precision):
         assert res <= 1.01e-9, (b, res)
         p1.close()
     pb.close()
+
+
+def test_graphs_come_with_the_second_solve_and_go_with_the_coarse_space():
+    """A small plan's first solve issues its launches, the second with the same arguments
+    captures a graph that the later ones replay, other arguments and a new coarse space start
+    over; every solve equals the plan without graphs bit for bit."""
+    sc = synth.raster_iqu(side=23, spp=8, interval_len=1058, seed_key=90, n_det=4, lam=64,
+                          fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+    pg = Plan.from_scan(sc, coarse=True, graph=True)
+    pn = Plan.from_scan(sc, coarse=True, graph=False)
+    b = pn.rhs(torch.from_numpy(sc.noise).cuda())
+
+    def same(tol, max_iter, times):
+        kw = dict(precond="2lvl", precision="fp64", tol=tol, max_iter=max_iter)
+        xn, i_n = pn.pcg_solve(b, **kw)
+        for k in range(times):
+            xg, ig = pg.pcg_solve(b, **kw)
+            assert torch.equal(xg, xn), (tol, max_iter, k)
+            assert ig["iterations"] == i_n["iterations"]
+            assert torch.equal(pg.apply_A(xg), pn.apply_A(xn))  # eager work between replays
+
+    same(1e-9, 2000, 4)
+    same(1e-6, 1999, 3)
+    for p in (pg, pn):
+        p.coarse_from_krylov(b, tol=1e-9, max_iter=2000, eps_tol=0.3)
+    same(1e-9, 2000, 3)
+    pg.close()
+    pn.close()
