@@ -137,6 +137,15 @@ struct PcgScalars {
     int pad;
 };
 
+// Work range of one P^T wave: the sorted samples [i0, i1) of the pixels [p0, p1) of a problem.
+// One aligned record, so that a wave has all of it after one scalar load.
+struct alignas(32) WaveRange {
+    int64_t i0, i1;
+    int32_t p0, p1;
+    int32_t prob;
+    int32_t pad;
+};
+
 // Control block of the PCG kernels (passed by value).  A batch of B independent problems
 // shares every launch; problem b owns the compact pixels [ooff[b], ooff[b+1]).  Vector
 // kernels map block g to (problem b, block k < kVecBlocks of b) through the block offsets
@@ -262,8 +271,7 @@ struct mm_plan_s {
     mm::DBuf<int64_t> seg;              // [n_obs+1] first sorted position of every pixel;
                                         // pixel c holds [seg[c], seg[c] + hits[c])
     mm::DBuf<uint64_t> heads;           // segment-start bit per sorted sample
-    mm::DBuf<int32_t> wave_pix;         // [n_waves+1] pixel ranges of the P^T waves
-    mm::DBuf<int32_t> wave_prob;        // [n_waves] problem of every wave
+    mm::DBuf<mm::WaveRange> wave_rng;   // [n_waves] work ranges of P^T
     mm::DBuf<int64_t> wave_off;         // [B+1] first P^T wave of every problem
     mm::DBuf<int64_t> soff;             // [B+1] h_soff on the device
     int64_t n_waves = 0;
@@ -388,7 +396,7 @@ int toeplitz_tod32(mm_plan_t pl, const void* y, int y_f64, float* z);
 // 10.3 / 22.3, 2^22 32.5 / 31.6, 2^24 105 / 109; FP32: 2^20 7.7 / 15.8, 2^22 15.9 / 18.8, 2^24
 // 54.8 / 57.3, 2^25 ring scan 159 / 164.
 constexpr int64_t kPtRange = 512;
-// P^T work ranges (wave_pix, wave_prob, wave_off) for per_wave samples per range; with
+// P^T work ranges (wave_rng, wave_off) for per_wave samples per range; with
 // min_waves > 0 a problem whose samples make fewer ranges takes smaller ones (halved down to
 // kPtRange), a rule on the problem alone so that its sums do not depend on the batch
 int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves = 0);

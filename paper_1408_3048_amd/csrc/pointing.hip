@@ -11,10 +11,44 @@
 namespace mm {
 namespace {
 
+// A lane's value from another lane by data-parallel primitives: row_shr:n (lane - n of the
+// same row of 16), row_bcast:15 / :31 (last lane of the row / of the two rows before the
+// lane's), wave_shr:1 (lane - 1); 0 where there is no such lane.
+constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143, kWaveShr1 = 0x138;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true),
+        __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float last_lane(float x) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ double last_lane(double x) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                            __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+
+// one step of the scan below: the lanes with `take` add the value of lane CTRL
+template <int CTRL, int NV, typename T>
+__device__ __forceinline__ void scan_step(T (&acc)[NV], bool take) {
+    if (__ballot(take) == 0) return;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        const T u = dpp<CTRL>(acc[q]);
+        acc[q] = take ? acc[q] + u : acc[q];
+    }
+}
+
 // Wave-level segmented reduction over pixel-sorted samples.
 //
-// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ... and walks
-// them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
+// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., counted from a
+// multiple of 64 at or below the first (32-bit positions: the caller moves its pointers
+// there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
 // (e < E), loaded with aligned vector loads so E gathers are in flight per lane.
 // Each lane first sums its own samples segment by segment, then one segmented
 // inclusive scan over the 64 lane summaries (flag: the lane holds a segment
@@ -24,7 +58,7 @@ namespace {
 // the plan, so results are deterministic; samples outside [i0, i1) are zeros.
 // `load(base, valid, v)` fills v[e][.] for the E samples; `emit(pixel, val)`.
 template <typename T, int NV, int E, class Load, class Emit>
-__device__ __forceinline__ void seg_reduce(int64_t i0, int64_t i1, int64_t p0,
+__device__ __forceinline__ void seg_reduce(int i0, int i1, int32_t p0,
                                            const unsigned long long* __restrict__ heads,
                                            Load&& load, Emit&& emit) {
     static_assert(64 % E == 0, "E must divide 64");
@@ -32,16 +66,16 @@ __device__ __forceinline__ void seg_reduce(int64_t i0, int64_t i1, int64_t p0,
     T carry[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) carry[q] = (T)0;
-    int64_t pprev = p0 - 1;
-    for (int64_t c = i0 & ~(int64_t)(E - 1); c < i1; c += 64 * E) {
-        const int64_t base = c + (int64_t)E * lane;
+    int32_t pprev = p0 - 1;
+    for (int c = i0 & ~(E - 1); c < i1; c += 64 * E) {
+        const int base = c + E * lane;
         bool valid[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) valid[e] = base + e >= i0 && base + e < i1;
         // segment-start words of the lane's samples and of the sample after them, loaded
         // unconditionally (a valid word for lanes past the range) ahead of the samples, so
         // that a chunk's loads are in flight together; their bits are read after load()
-        const int64_t inext = base + E;
+        const int inext = base + E;
         const unsigned long long hw = heads[(base < i1 ? base : i0) >> 6];
         const unsigned long long hn = heads[(inext < i1 ? inext : i0) >> 6];
         T v[E][NV];
@@ -65,46 +99,42 @@ __device__ __forceinline__ void seg_reduce(int64_t i0, int64_t i1, int64_t p0,
 #pragma unroll
             for (int q = 0; q < NV; ++q) sl[e][q] = run[q];
         }
-        // segmented inclusive scan over lanes of (any, run)
+        // Segmented inclusive scan of run over the lanes: `dist` lanes before this one belong
+        // to its last segment (all of them if no segment starts up to here), so a step adds
+        // the partial sum of a lane d before where dist >= d.  Rows of 16 lanes first, then
+        // the rows; steps that no lane needs are left out.
         T acc[NV];
 #pragma unroll
         for (int q = 0; q < NV; ++q) acc[q] = run[q];
-        int f = any ? 1 : 0;
-        int hc = __popc(hb), hcs = hc;
+        const unsigned long long hl = __ballot(any);
+        const int dist = lane - (63 - __clzll((long long)((hl | 1ull) & (~0ull >> (63 - lane)))));
+        const int r16 = lane & 15, r32 = lane & 31;
+        scan_step<kRowShr + 1>(acc, r16 >= 1 && dist >= 1);
+        scan_step<kRowShr + 2>(acc, r16 >= 2 && dist >= 2);
+        scan_step<kRowShr + 4>(acc, r16 >= 4 && dist >= 4);
+        scan_step<kRowShr + 8>(acc, r16 >= 8 && dist >= 8);
+        scan_step<kRowBcast15>(acc, (lane & 16) != 0 && dist > r16);
+        scan_step<kRowBcast31>(acc, (lane & 32) != 0 && dist > r32);
+        // segment starts in the lanes before this one
+        int hex = 0, hall = 0;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            T u[NV];
-#pragma unroll
-            for (int q = 0; q < NV; ++q) u[q] = __shfl_up(acc[q], d);
-            const int fu = __shfl_up(f, d);
-            const int cu = __shfl_up(hcs, d);
-            if (lane >= d) {
-                if (!f) {
-#pragma unroll
-                    for (int q = 0; q < NV; ++q) acc[q] += u[q];
-                }
-                f |= fu;
-                hcs += cu;
-            }
+        for (int e = 0; e < E; ++e) {
+            const unsigned long long he = __ballot((hb >> e) & 1u);
+            hex = __builtin_amdgcn_mbcnt_hi((uint32_t)(he >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((uint32_t)he, hex));
+            hall += __popcll(he);
         }
         // partial sum entering this lane (from earlier lanes and the previous chunk)
         T pre[NV];
-        int fex = __shfl_up(f, 1);
 #pragma unroll
-        for (int q = 0; q < NV; ++q) pre[q] = __shfl_up(acc[q], 1);
-        if (lane == 0) {
-            fex = 0;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) pre[q] = (T)0;
-        }
-        if (!fex) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q) pre[q] += carry[q];
+        for (int q = 0; q < NV; ++q) {
+            const T u = dpp<kWaveShr1>(acc[q]);
+            pre[q] = hex == 0 ? u + carry[q] : u;
         }
         // segment ends and totals
         const bool next_head_last =
             valid[E - 1] && inext < i1 && ((hn >> (inext & 63)) & 1ull) != 0;
-        int64_t pix = pprev + (hcs - hc);
+        int32_t pix = pprev + hex;
         T last[NV];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -112,7 +142,7 @@ __device__ __forceinline__ void seg_reduce(int64_t i0, int64_t i1, int64_t p0,
             T tot[NV];
 #pragma unroll
             for (int q = 0; q < NV; ++q) tot[q] = seen[e] ? sl[e][q] : sl[e][q] + pre[q];
-            const int64_t i = base + e;
+            const int i = base + e;
             bool end = false;
             if (valid[e]) {
                 if (i + 1 == i1) end = true;
@@ -126,8 +156,8 @@ __device__ __forceinline__ void seg_reduce(int64_t i0, int64_t i1, int64_t p0,
             }
         }
 #pragma unroll
-        for (int q = 0; q < NV; ++q) carry[q] = __shfl(last[q], 63);
-        pprev += __shfl(hcs, 63);
+        for (int q = 0; q < NV; ++q) carry[q] = last_lane(last[q]);
+        pprev += hall;
     }
 }
 
@@ -157,34 +187,47 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// index of the wave within its block, in a scalar register (what depends on it is loaded by
+// scalar loads)
+__device__ __forceinline__ int wave_of_block() {
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
 // x[p, s] = sum_{t in p} W[t, s] z_t (P^T), E samples per lane (a multiple of 4).  The z
 // gather of a chunk of 64 E sorted samples is issued lane-strided (one instruction covers
 // 64 consecutive sorted samples, i.e. a few runs of consecutive time samples, so few cache
 // lines) and handed to the lane layout of the segmented reduction (E consecutive samples
 // per lane) through LDS; the additions are unchanged.
+// Small problems are bound by the serial chain of a wave (its range, indices, gathers, the
+// scan), large ones by the sorted streams, gathers that take a cache line for a few samples by
+// the lines.  The range comes in one scalar load, positions count from it in 32 bits and the
+// scan goes lane to lane by DPP instead of through LDS: FP64 at 2^14 / 2^20 / 2^22 samples
+// 5.75 / 11.6 / 35.0 -> 4.9 / 10.9 / 31.5 us, FP32 at 2^20 / 2^24 7.8 / 58.2 -> 6.5 / 56.0 us,
+// ring scan of 2^25 174 -> 170, 8 columns at 2^24 254 -> 240, block sums of M_BD with them.
 template <typename T, int NS, int E>
-__global__ __launch_bounds__(256) void k_scatter(const int32_t* __restrict__ perm,
+__global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scatter(const int32_t* __restrict__ perm,
                                                  const T* __restrict__ ws, const T* __restrict__ z,
                                                  const unsigned long long* __restrict__ heads,
-                                                 const int32_t* __restrict__ wave_pix,
-                                                 const int64_t* __restrict__ seg,
-                                                 const int32_t* __restrict__ hits, int64_t n_waves,
-                                                 double* __restrict__ out,
-                                                 const int* __restrict__ mask,
-                                                 const int32_t* __restrict__ wave_prob) {
+                                                 const WaveRange* __restrict__ rng,
+                                                 int64_t n_waves, double* __restrict__ out,
+                                                 const int* __restrict__ mask) {
     static_assert(E % 4 == 0, "E must be a multiple of 4");
     __shared__ __align__(16) T zx[4][64 * E];
     // the blocks of one XCD take a contiguous range of waves (neighbouring pixels share the
     // time samples whose z they gather)
     const int64_t blk = xcd_item(blockIdx.x, (n_waves + 3) / 4);
     if (blk < 0) return;
-    const int64_t w = blk * 4 + (threadIdx.x >> 6);
+    const int64_t w = blk * 4 + wave_of_block();
     if (w >= n_waves) return;
-    if (mask && !mask[wave_prob[w]]) return;
-    const int32_t p0 = wave_pix[w], p1 = wave_pix[w + 1];
-    if (p0 >= p1) return;
-    const int64_t i0 = seg[p0];
-    const int64_t i1 = seg[p1 - 1] + hits[p1 - 1];
+    const WaveRange wr = rng[w];
+    if (wr.p0 >= wr.p1) return;
+    if (mask && !mask[wr.prob]) return;
+    // positions from a multiple of 64
+    const int64_t c0 = wr.i0 & ~(int64_t)63;
+    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    perm += c0;
+    ws += 2 * c0;
+    heads += c0 >> 6;
     const int lane = threadIdx.x & 63;
     T* zw = zx[threadIdx.x >> 6];
     // sample indices of the next chunk, loaded one chunk ahead (-1 outside [i0, i1)).  The
@@ -193,17 +236,17 @@ __global__ __launch_bounds__(256) void k_scatter(const int32_t* __restrict__ per
     // guarded loads become one branch each, and the compiler then waits for every load
     // before issuing the next.
     int32_t pf[E];
-    auto fetch = [&](int64_t c) {
+    auto fetch = [&](int c) {
 #pragma unroll
         for (int g = 0; g < E; ++g) {
-            const int64_t i = c + lane + 64 * g;
+            const int i = c + lane + 64 * g;
             const bool in = i >= i0 && i < i1;
             const int32_t t = ld_stream(perm + (in ? i : i0));
             pf[g] = in ? t : -1;
         }
     };
-    fetch(i0 & ~(int64_t)(E - 1));
-    auto load = [&](int64_t base, const bool* valid, T (*v)[NS]) {
+    fetch(i0 & ~(E - 1));
+    auto load = [&](int base, const bool* valid, T (*v)[NS]) {
         // the sorted weights are loaded first, so their latency overlaps the z gather's
         // (loads after the exchange below would wait for it); lanes past the range skip them
         T wv[2 * E];
@@ -232,7 +275,7 @@ __global__ __launch_bounds__(256) void k_scatter(const int32_t* __restrict__ per
             }
         }
         // every lane takes part in the exchange, also lanes past the range
-        const int64_t c = base - (int64_t)E * lane;
+        const int c = base - E * lane;
         int32_t tc[E];
 #pragma unroll
         for (int g = 0; g < E; ++g) tc[g] = pf[g];
@@ -268,11 +311,11 @@ __global__ __launch_bounds__(256) void k_scatter(const int32_t* __restrict__ per
             for (int e = 0; e < E; ++e) v[e][0] = zz[e];
         }
     };
-    auto emit = [&](int64_t pix, const T* tot) {
+    auto emit = [&](int32_t pix, const T* tot) {
 #pragma unroll
-        for (int q = 0; q < NS; ++q) out[pix * NS + q] = (double)tot[q];
+        for (int q = 0; q < NS; ++q) out[(int64_t)pix * NS + q] = (double)tot[q];
     };
-    seg_reduce<T, NS, E>(i0, i1, p0, heads, load, emit);
+    seg_reduce<T, NS, E>(i0, i1, wr.p0, heads, load, emit);
 }
 
 // P^T of NC FP32 time streams z + k zstride (k < NC), the A Z columns of the coarse space
@@ -285,41 +328,43 @@ template <int NS, int E, int NC>
 __global__ __launch_bounds__(256) void k_scatter_cols(
     const int32_t* __restrict__ perm, const float* __restrict__ ws, const float* __restrict__ z,
     int64_t zstride, int nc, const unsigned long long* __restrict__ heads,
-    const int32_t* __restrict__ wave_pix, const int64_t* __restrict__ seg,
-    const int32_t* __restrict__ hits, int64_t n_waves, const int32_t* __restrict__ wave_prob,
-    const int64_t* __restrict__ ooff, const int32_t* __restrict__ ncols,
+    const WaveRange* __restrict__ rng, int64_t n_waves, const int64_t* __restrict__ ooff, const int32_t* __restrict__ ncols,
     const int64_t* __restrict__ blk_off, int k0, float* __restrict__ az) {
     static_assert(E % 4 == 0, "E must be a multiple of 4");
     constexpr int NV = NC * NS;
     __shared__ __align__(16) float zx[4][NC][64 * E];
     const int64_t blk = xcd_item(blockIdx.x, (n_waves + 3) / 4);
     if (blk < 0) return;
-    const int64_t w = blk * 4 + (threadIdx.x >> 6);
+    const int64_t w = blk * 4 + wave_of_block();
     if (w >= n_waves) return;
-    const int b = wave_prob[w];
+    const WaveRange wr = rng[w];
+    const int b = wr.prob;
     int ncb = ncols[b] - k0;  // columns this problem has in the group
     ncb = ncb < nc ? ncb : nc;
     if (ncb <= 0) return;
-    const int32_t p0 = wave_pix[w], p1 = wave_pix[w + 1];
-    if (p0 >= p1) return;
+    if (wr.p0 >= wr.p1) return;
     const int64_t q0 = ooff[b], n_vec = (ooff[b + 1] - q0) * NS;
     float* const azb = az + blk_off[b] + (int64_t)k0 * n_vec - q0 * NS;  // pixel q0 at 0
-    const int64_t i0 = seg[p0];
-    const int64_t i1 = seg[p1 - 1] + hits[p1 - 1];
+    // positions from a multiple of 64
+    const int64_t c0 = wr.i0 & ~(int64_t)63;
+    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    perm += c0;
+    ws += 2 * c0;
+    heads += c0 >> 6;
     const int lane = threadIdx.x & 63;
     float (*zw)[64 * E] = zx[threadIdx.x >> 6];
     int32_t pf[E];
-    auto fetch = [&](int64_t c) {
+    auto fetch = [&](int c) {
 #pragma unroll
         for (int g = 0; g < E; ++g) {
-            const int64_t i = c + lane + 64 * g;
+            const int i = c + lane + 64 * g;
             const bool in = i >= i0 && i < i1;
             const int32_t t = ld_stream(perm + (in ? i : i0));
             pf[g] = in ? t : -1;
         }
     };
-    fetch(i0 & ~(int64_t)(E - 1));
-    auto load = [&](int64_t base, const bool* valid, float (*v)[NV]) {
+    fetch(i0 & ~(E - 1));
+    auto load = [&](int base, const bool* valid, float (*v)[NV]) {
         float wv[2 * E];
         if constexpr (NS == 3) {
             if (base < i1) {
@@ -336,7 +381,7 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
                 for (int e = 0; e < 2 * E; ++e) wv[e] = 0.0f;
             }
         }
-        const int64_t c = base - (int64_t)E * lane;
+        const int c = base - E * lane;
         int32_t tc[E];
 #pragma unroll
         for (int g = 0; g < E; ++g) tc[g] = pf[g];
@@ -380,8 +425,8 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
                 }
             }
     };
-    auto emit = [&](int64_t pix, const float* tot) {
-        float* dst = azb + pix * NS;
+    auto emit = [&](int32_t pix, const float* tot) {
+        float* dst = azb + (int64_t)pix * NS;
 #pragma unroll
         for (int k = 0; k < NC; ++k)
             if (k < ncb) {
@@ -389,7 +434,7 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
                 for (int q = 0; q < NS; ++q) dst[k * n_vec + q] = tot[NS * k + q];
             }
     };
-    seg_reduce<float, NV, E>(i0, i1, p0, heads, load, emit);
+    seg_reduce<float, NV, E>(i0, i1, wr.p0, heads, load, emit);
 }
 
 // y_t = sum_s W[t, s] x[c(t), s]
@@ -425,27 +470,30 @@ __device__ __forceinline__ int32_t interval_of(const int64_t* __restrict__ lo, i
 template <int NV>
 __global__ __launch_bounds__(256) void k_bj_build(
     const int32_t* __restrict__ perm, const double* __restrict__ ws,
-    const unsigned long long* __restrict__ heads, const int32_t* __restrict__ wave_pix,
-    const int64_t* __restrict__ seg, const int32_t* __restrict__ hits, int64_t n_waves,
-    const int64_t* __restrict__ int_lo,
+    const unsigned long long* __restrict__ heads, const WaveRange* __restrict__ rng,
+    int64_t n_waves, const int64_t* __restrict__ int_lo,
     int32_t n_int, const int32_t* __restrict__ int_kern, const double* __restrict__ t0,
     double rcond_min, double* __restrict__ bj, int* __restrict__ bad, double* __restrict__ rc_out) {
     constexpr int E = 4;
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t w = (int64_t)blockIdx.x * 4 + wave_of_block();
     if (w >= n_waves) return;
-    const int32_t p0 = wave_pix[w], p1 = wave_pix[w + 1];
-    if (p0 >= p1) return;
+    const WaveRange wr = rng[w];
+    if (wr.p0 >= wr.p1) return;
     // a pixel's sorted samples come in time-ordered runs within one interval: the lane keeps
     // the interval [jlo, jhi) and t_0 of its last sample and searches only outside it
     int64_t jlo = 0, jhi = 0;
     double dj = 0.0;
-    const int64_t s0 = seg[p0];  // a valid sorted position for the unconditional loads
-    auto load = [&](int64_t base, const bool* valid, double (*v)[NV]) {
+    const int64_t c0 = wr.i0 & ~(int64_t)63;  // positions from a multiple of 64
+    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    perm += c0;
+    ws += 2 * c0;
+    heads += c0 >> 6;
+    auto load = [&](int base, const bool* valid, double (*v)[NV]) {
         int64_t tt[E];
         double wa[E], wb[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int64_t ic = valid[e] ? base + e : s0;
+            const int64_t ic = valid[e] ? base + e : i0;  // a valid position for all
             tt[e] = perm[ic];
             if constexpr (NV == 6) {
                 wa[e] = ws[2 * ic];
@@ -480,7 +528,8 @@ __global__ __launch_bounds__(256) void k_bj_build(
             }
         }
     };
-    auto emit = [&](int64_t c, const double* B) {
+    auto emit = [&](int32_t pix, const double* B) {
+        const int64_t c = pix;
         double rc;
         if constexpr (NV == 1) {
             bj[c] = 1.0 / B[0];
@@ -514,7 +563,7 @@ __global__ __launch_bounds__(256) void k_bj_build(
         if (rc_out) rc_out[c] = rc;
         if (!(rc >= rcond_min)) atomicMin(bad, (int)c);
     };
-    seg_reduce<double, NV, E>(seg[p0], seg[p1 - 1] + hits[p1 - 1], p0, heads, load, emit);
+    seg_reduce<double, NV, E>(i0, i1, wr.p0, heads, load, emit);
 }
 
 // z = M_BD r per pixel of every masked problem (+ partials of r^T z for the PCG)
@@ -558,12 +607,12 @@ int scatter_t(mm_plan_t pl, const T* z, const T* ws, double* x, const int* mask)
     constexpr int E = 4;
     if (pl->n_s == 3)
         hipLaunchKernelGGL((k_scatter<T, 3, E>), dim3(xcd_grid(nb)), dim3(256), 0, pl->stream, pl->perm.p, ws,
-                           z, (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, x, mask, pl->wave_prob.p);
+                           z, (const unsigned long long*)pl->heads.p, pl->wave_rng.p, pl->n_waves,
+                           x, mask);
     else
         hipLaunchKernelGGL((k_scatter<T, 1, E>), dim3(xcd_grid(nb)), dim3(256), 0, pl->stream, pl->perm.p, ws,
-                           z, (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, x, mask, pl->wave_prob.p);
+                           z, (const unsigned long long*)pl->heads.p, pl->wave_rng.p, pl->n_waves,
+                           x, mask);
     MM_HIP(hipGetLastError());
     return MM_OK;
 }
@@ -582,14 +631,14 @@ int scatter_cols32(mm_plan_t pl, const float* z, int64_t zstride, int nc, int k0
     if (pl->n_s == 3)
         hipLaunchKernelGGL((k_scatter_cols<3, E, kScatterCols>), dim3(xcd_grid(nb)), dim3(256), 0,
                            pl->stream, pl->perm.p, pl->ws32.p, z, zstride, nc,
-                           (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, pl->wave_prob.p, pl->ooff.p, ncols, blk_off,
+                           (const unsigned long long*)pl->heads.p, pl->wave_rng.p,
+                           pl->n_waves, pl->ooff.p, ncols, blk_off,
                            k0, az);
     else
         hipLaunchKernelGGL((k_scatter_cols<1, E, kScatterCols>), dim3(xcd_grid(nb)), dim3(256), 0,
                            pl->stream, pl->perm.p, pl->ws32.p, z, zstride, nc,
-                           (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, pl->wave_prob.p, pl->ooff.p, ncols, blk_off,
+                           (const unsigned long long*)pl->heads.p, pl->wave_rng.p,
+                           pl->n_waves, pl->ooff.p, ncols, blk_off,
                            k0, az);
     MM_HIP(hipGetLastError());
     return MM_OK;
@@ -626,14 +675,14 @@ int build_bj(mm_plan_t pl) {
     const int64_t nb = (pl->n_waves + 3) / 4;
     if (pl->n_s == 3)
         hipLaunchKernelGGL(k_bj_build<6>, dim3(nb), dim3(256), 0, st, pl->perm.p, pl->ws64.p,
-                           (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, pl->int_lo.p, pl->n_int, pl->int_kern.p,
+                           (const unsigned long long*)pl->heads.p, pl->wave_rng.p,
+                           pl->n_waves, pl->int_lo.p, pl->n_int, pl->int_kern.p,
                            pl->kern_t0.p,
                            pl->opts.rcond_min, pl->bj.p, bad.p, rc.p);
     else
         hipLaunchKernelGGL(k_bj_build<1>, dim3(nb), dim3(256), 0, st, pl->perm.p, pl->ws64.p,
-                           (const unsigned long long*)pl->heads.p, pl->wave_pix.p, pl->seg.p,
-                           pl->hits.p, pl->n_waves, pl->int_lo.p, pl->n_int, pl->int_kern.p,
+                           (const unsigned long long*)pl->heads.p, pl->wave_rng.p,
+                           pl->n_waves, pl->int_lo.p, pl->n_int, pl->int_kern.p,
                            pl->kern_t0.p,
                            pl->opts.rcond_min, pl->bj.p, bad.p, rc.p);
     MM_HIP(hipGetLastError());

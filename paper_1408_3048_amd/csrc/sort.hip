@@ -268,27 +268,34 @@ __global__ void k_prob_minmax(const int32_t* __restrict__ pix, int64_t n,
 }
 
 // P^T work ranges: the sorted samples of problem b (from its padded start soff[b]) are cut
-// at soff[b] + k pw[b], each wave taking whole pixels; wave w belongs to problem wprob[w]
-__global__ void k_wave_ranges(const int64_t* __restrict__ seg, const int64_t* __restrict__ ooff,
-                              const int64_t* __restrict__ soff, const int64_t* __restrict__ woff,
-                              const int64_t* __restrict__ pw, int B, int64_t n_obs,
-                              int64_t n_waves,
-                              int32_t* __restrict__ wp, int32_t* __restrict__ wprob) {
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w <= n_waves;
+// at soff[b] + k pw[b], each wave taking the whole pixels that start in its range
+__global__ void k_wave_ranges(const int64_t* __restrict__ seg, const int32_t* __restrict__ hits,
+                              const int64_t* __restrict__ ooff, const int64_t* __restrict__ soff,
+                              const int64_t* __restrict__ woff, const int64_t* __restrict__ pw,
+                              int B, int64_t n_waves, WaveRange* __restrict__ rng) {
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < n_waves;
          w += (int64_t)gridDim.x * blockDim.x) {
-        if (w == n_waves) {
-            wp[w] = (int32_t)n_obs;
-            continue;
-        }
         const int b = find_range(woff, B, w);
-        wprob[w] = b;
-        const int64_t target = soff[b] + (w - woff[b]) * pw[b];
-        int64_t lo = ooff[b], hi = ooff[b + 1];  // first c in [ooff[b], ooff[b+1]] with seg[c] >= target
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (seg[mid] >= target) hi = mid; else lo = mid + 1;
-        }
-        wp[w] = (int32_t)lo;
+        // first c in [ooff[b], ooff[b+1]] with seg[c] >= the start of range k of the problem
+        auto first = [&](int64_t k) {
+            const int64_t target = soff[b] + k * pw[b];
+            int64_t lo = ooff[b], hi = ooff[b + 1];
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (seg[mid] >= target) hi = mid; else lo = mid + 1;
+            }
+            return lo;
+        };
+        const int64_t k = w - woff[b];
+        const int64_t p0 = first(k), p1 = w + 1 < woff[b + 1] ? first(k + 1) : ooff[b + 1];
+        WaveRange r;
+        r.i0 = p0 < p1 ? seg[p0] : 0;
+        r.i1 = p0 < p1 ? seg[p1 - 1] + hits[p1 - 1] : 0;
+        r.p0 = (int32_t)p0;
+        r.p1 = (int32_t)p1;
+        r.prob = b;
+        r.pad = 0;
+        rng[w] = r;
     }
 }
 
@@ -620,11 +627,10 @@ int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves) {
     MM_HIP(hipMemcpyAsync(d_pw.p, pw.data(), B * 8, hipMemcpyHostToDevice, st));
     MM_TRY(pl->wave_off.alloc(B + 1));
     MM_HIP(hipMemcpyAsync(pl->wave_off.p, woff.data(), (B + 1) * 8, hipMemcpyHostToDevice, st));
-    MM_TRY(pl->wave_pix.alloc(pl->n_waves + 1));
-    MM_TRY(pl->wave_prob.alloc(std::max<int64_t>(1, pl->n_waves)));
-    hipLaunchKernelGGL(k_wave_ranges, dim3(grid_for(pl->n_waves + 1)), dim3(256), 0, st, pl->seg.p,
-                       pl->ooff.p, pl->soff.p, pl->wave_off.p, d_pw.p, B, pl->n_obs, pl->n_waves,
-                       pl->wave_pix.p, pl->wave_prob.p);
+    MM_TRY(pl->wave_rng.alloc(std::max<int64_t>(1, pl->n_waves)));
+    hipLaunchKernelGGL(k_wave_ranges, dim3(grid_for(pl->n_waves)), dim3(256), 0, st, pl->seg.p,
+                       pl->hits.p, pl->ooff.p, pl->soff.p, pl->wave_off.p, d_pw.p, B, pl->n_waves,
+                       pl->wave_rng.p);
     MM_HIP(hipGetLastError());
     return MM_OK;
 }

@@ -235,3 +235,31 @@ def test_graphs_come_with_the_second_solve_and_go_with_the_coarse_space():
     same(1e-9, 2000, 3)
     pg.close()
     pn.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("ns", [1, 3])
+def test_segmented_sums_of_every_run_length(ns, dtype):
+    """P^T over pixels of 1 (I) or 4 (IQU) to 1300 samples: runs that start and end at every
+    lane, row of 16 lanes and 256-sample chunk, empty work ranges, pixels of several ranges.
+    The sums are of small integers, so they are exact in any order."""
+    r = np.random.default_rng(17)
+    step = 1 if ns == 1 else 4
+    hits = np.concatenate([np.arange(step, 70 * step, step), [1024, 252, 4, 256, 4, 260, 1300],
+                           r.integers(1, 9, 600) * step, np.full(300, step)])
+    pix = np.repeat(np.arange(hits.size), hits)
+    order = r.permutation(pix.size)
+    k = np.concatenate([np.arange(h) % 4 for h in hits])
+    q = np.array([1.0, 0.0, -1.0, 0.0])[k]
+    u = np.array([0.0, 1.0, 0.0, -1.0])[k]
+    pix, w = pix[order].astype(np.int32), np.stack([q, u], 1)[order]
+    n = pix.size
+    plan = Plan(torch.from_numpy(pix).cuda(), torch.from_numpy(w).cuda() if ns == 3 else None,
+                hits.size, np.array([0, n]), np.array([[1.0, 0.1, 1.0]]), n_stokes=ns, lam=8,
+                precision="mixed")
+    z = r.integers(-8, 9, n).astype(np.float64)
+    got = plan.apply_PT(torch.from_numpy(z).to(dtype).cuda()).cpu().numpy().reshape(-1, ns)
+    cols = [np.ones(n), w[:, 0], w[:, 1]][:ns]
+    want = np.stack([np.bincount(pix, z * c, hits.size) for c in cols], 1)
+    assert np.array_equal(got, want)
+    plan.close()
