@@ -39,12 +39,15 @@ namespace {
 // each.  Requests are rounded up to a size class (1/8 of their power of two); a freed block
 // is kept per device and class with an event recorded on the freeing stream, and the
 // allocation that reuses it makes its own stream wait on that event, so reuse is
-// stream-ordered whatever the streams.  At most kCacheCap bytes are kept per device; past
+// stream-ordered whatever the streams.  A block freed on the default stream, which is never
+// destroyed, has no event (recording one takes about 2 us, and a plan with its release makes
+// about 130): the default stream's own order covers its reuse there, and an allocation for
+// another stream records the event then.  At most kCacheCap bytes are kept per device; past
 // that, and when the device runs out of memory, blocks go back to the pool.  No allocation
 // or release happens inside a captured stream region.
 struct CachedBlock {
     void* p;
-    hipEvent_t ev;
+    hipEvent_t ev;  // nullptr: freed on the default stream
 };
 struct LiveBlock {
     int dev;
@@ -69,6 +72,10 @@ void flush_cache(int dev, hipStream_t st) {
     for (auto& kv : g_cache) {
         if (kv.first.first != dev) continue;
         for (const CachedBlock& c : kv.second) {
+            if (!c.ev) {
+                (void)hipFreeAsync(c.p, nullptr);
+                continue;
+            }
             (void)hipStreamWaitEvent(st, c.ev, 0);
             (void)hipFreeAsync(c.p, st);
             g_events[dev].push_back(c.ev);
@@ -76,6 +83,37 @@ void flush_cache(int dev, hipStream_t st) {
         kv.second.clear();
     }
     g_cached_bytes[dev] = 0;
+}
+
+// an event of device dev, from the idle ones or new (g_cache_mu held); nullptr on failure
+hipEvent_t take_event(int dev) {
+    hipEvent_t ev = nullptr;
+    auto& idle = g_events[dev];
+    if (!idle.empty()) {
+        ev = idle.back();
+        idle.pop_back();
+    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+        return nullptr;
+    }
+    return ev;
+}
+
+// what stream st has to wait for before it uses a cached block
+hipError_t wait_cached(const CachedBlock& c, int dev, hipStream_t st) {
+    hipEvent_t ev = c.ev;
+    if (!ev) {
+        if (st == nullptr) return hipSuccess;
+        ev = take_event(dev);
+        if (!ev) return hipErrorOutOfMemory;
+        const hipError_t e = hipEventRecord(ev, nullptr);
+        if (e != hipSuccess) {
+            g_events[dev].push_back(ev);
+            return e;
+        }
+    }
+    const hipError_t e = hipStreamWaitEvent(st, ev, 0);
+    g_events[dev].push_back(ev);
+    return e;
 }
 
 }  // namespace
@@ -99,10 +137,9 @@ int pool_alloc(void** p, size_t bytes, hipStream_t st) {
         const CachedBlock c = it->second.back();
         it->second.pop_back();
         g_cached_bytes[dev] -= cls;
-        g_events[dev].push_back(c.ev);
-        const hipError_t e = hipStreamWaitEvent(st, c.ev, 0);
+        const hipError_t e = wait_cached(c, dev, st);
         if (e != hipSuccess) {
-            (void)hipFreeAsync(c.p, st);
+            (void)hipFreeAsync(c.p, c.ev ? st : nullptr);
             set_error("hipStreamWaitEvent failed: %s", hipGetErrorString(e));
             return MM_ERR_DEVICE;
         }
@@ -140,21 +177,58 @@ void pool_free(void* p, hipStream_t st) {
         return;
     }
     hipEvent_t ev = nullptr;
-    auto& idle = g_events[b.dev];
-    if (!idle.empty()) {
-        ev = idle.back();
-        idle.pop_back();
-    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-        (void)hipFreeAsync(p, st);
-        return;
-    }
-    if (hipEventRecord(ev, st) != hipSuccess) {
-        idle.push_back(ev);
-        (void)hipFreeAsync(p, st);
-        return;
+    if (st != nullptr) {
+        ev = take_event(b.dev);
+        if (!ev || hipEventRecord(ev, st) != hipSuccess) {
+            if (ev) g_events[b.dev].push_back(ev);
+            (void)hipFreeAsync(p, st);
+            return;
+        }
     }
     g_cache[{b.dev, b.cls}].push_back({p, ev});
     g_cached_bytes[b.dev] += b.cls;
+}
+
+// Page-locked host blocks for the plans' state mirrors, kept like the device blocks: the
+// runtime takes about 40 us to give one and as long to take it back.  A block comes back when
+// its plan's stream has been waited for, so no copy into it is under way; at most kPinnedCap
+// bytes of them are kept.
+constexpr size_t kPinnedCap = (size_t)1 << 20;
+std::multimap<size_t, void*> g_pinned;  // by size class (g_cache_mu)
+size_t g_pinned_bytes = 0;
+
+int pinned_alloc(void** p, size_t bytes) {
+    const size_t cls = size_class(bytes);
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        auto it = g_pinned.find(cls);
+        if (it != g_pinned.end()) {
+            *p = it->second;
+            g_pinned.erase(it);
+            g_pinned_bytes -= cls;
+            return MM_OK;
+        }
+    }
+    if (hipHostMalloc(p, cls, hipHostMallocPortable) != hipSuccess) {
+        *p = nullptr;
+        set_error("hipHostMalloc failed");
+        return MM_ERR_DEVICE;
+    }
+    return MM_OK;
+}
+
+void pinned_free(void* p, size_t bytes) {
+    if (!p) return;
+    const size_t cls = size_class(bytes);
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        if (g_pinned_bytes + cls <= kPinnedCap) {
+            g_pinned.emplace(cls, p);
+            g_pinned_bytes += cls;
+            return;
+        }
+    }
+    (void)hipHostFree(p);
 }
 
 // RAII: the stream for allocations made during one API call
@@ -507,7 +581,6 @@ int check_vec_args(mm_plan_t pl, const void* a, const void* b) {
 using namespace mm;
 
 mm_plan_s::~mm_plan_s() {
-    if (h_sc) (void)hipHostFree(h_sc);
     for (auto& row : gexec)
         for (auto& g : row)
             if (g) (void)hipGraphExecDestroy(g);
@@ -515,6 +588,7 @@ mm_plan_s::~mm_plan_s() {
         (void)hipStreamSynchronize(gstream);
         (void)hipStreamDestroy(gstream);
     }
+    pinned_free(h_sc, sizeof(PcgScalars) * n_prob);
     for (auto& v : prof_ev)
         for (auto& r : v) {
             (void)hipEventDestroy(r.a);
@@ -706,12 +780,8 @@ int mm_plan_batched(mm_plan_t* out, int32_t n_problems, const int32_t* problem_i
     if ((s = pl->sc.alloc(pl->n_prob)) != MM_OK) return fail(s);
     if ((s = pl->act.alloc(pl->n_prob)) != MM_OK) return fail(s);
     if ((s = pl->sel.alloc(pl->n_prob)) != MM_OK) return fail(s);
-    if (hipHostMalloc((void**)&pl->h_sc, sizeof(PcgScalars) * pl->n_prob, hipHostMallocDefault) !=
-        hipSuccess) {
-        pl->h_sc = nullptr;
-        set_error("hipHostMalloc failed");
-        return fail(MM_ERR_DEVICE);
-    }
+    if ((s = pinned_alloc((void**)&pl->h_sc, sizeof(PcgScalars) * pl->n_prob)) != MM_OK)
+        return fail(s);
     if ((s = ensure_solver_buffers(pl, 1000)) != MM_OK) return fail(s);
     tick("buffers");
     if (opts->coarse == MM_COARSE_ZS && (s = build_coarse(pl)) != MM_OK) return fail(s);
@@ -1015,12 +1085,20 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
     }
     std::vector<int> status(B, MM_OK);
     std::vector<std::vector<double>> hist_all(B);
-    auto fetch_hist = [&](int bprob, int len, double scale) -> int {
-        if (len <= 0) return MM_OK;
-        std::vector<double> h(len);
-        MM_HIP(hipMemcpy(h.data(), pl->hist.p + (size_t)bprob * pl->hstride, len * 8,
-                         hipMemcpyDeviceToHost));
-        for (double v : h) hist_all[bprob].push_back(v * scale);
+    auto wanted = [&](int i) { return inf[i].history && inf[i].history_cap > 0; };
+    // the recorded residuals of the problems that asked for them, in one copy
+    auto fetch_hist = [&](double scale) -> int {
+        size_t len = 0;
+        for (int i = 0; i < B; ++i)
+            if (wanted(i)) len = std::max<size_t>(len, std::max(pl->h_sc[i].iter, 0));
+        if (len == 0) return MM_OK;
+        std::vector<double> h(len * B);
+        MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, pl->hist.p, (size_t)pl->hstride * 8, len * 8, B,
+                                hipMemcpyDeviceToHost, pl->stream));
+        MM_HIP(hipStreamSynchronize(pl->stream));
+        for (int i = 0; i < B; ++i)
+            for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)
+                hist_all[i].push_back(h[i * len + k] * scale);
         return MM_OK;
     };
     if (precision == MM_FP64 || precision == MM_MIXED) {
@@ -1041,8 +1119,8 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
             inf[i].replacements = sc.evals;
             status[i] = sc.state == kDone ? MM_OK
                         : sc.state == kBreakdown ? MM_ERR_BREAKDOWN : MM_ERR_NOCONV;
-            MM_TRY(fetch_hist(i, sc.iter, 1.0));
         }
+        MM_TRY(fetch_hist(1.0));
     } else {
         // iterative refinement: r = b - A64 x; solve A32 d = r by PCG from d = 0; x += d
         std::vector<double> bb;
@@ -1077,7 +1155,7 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
             MM_TRY(pcg_engine(pl, rout, d, ea));
             MM_TRY(read_scalars(pl));
             const PcgScalars& sc = pl->h_sc[0];
-            MM_TRY(fetch_hist(0, sc.iter, rel));  // relative to ||b||
+            MM_TRY(fetch_hist(rel));  // relative to ||b||
             total += sc.iter;
             MM_TRY(vec_axpby(pl, 1.0, x, 1.0, d, x));
             if (sc.state == kBreakdown) {

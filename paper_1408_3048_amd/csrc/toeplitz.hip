@@ -21,6 +21,7 @@
 // so no explicit permutation pass is needed.  Both transforms run as radix-16
 // passes held in registers with one LDS exchange per pass.
 #include <cmath>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -1220,39 +1221,36 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
         kpar[3 * g + 1] = pl->h_kern_psd[g].f_knee;
         kpar[3 * g + 2] = pl->h_kern_psd[g].alpha;
     }
-    DBuf<int32_t> d_klen;
-    DBuf<double> d_kpar, d_a;
-    DBuf<int64_t> d_aoff, d_acnt, d_nper, d_jcnt, d_toff, d_tcnt;
-    MM_TRY(d_klen.alloc(nk));
-    MM_TRY(d_kpar.alloc(3 * nk));
+    // the kernels' tables, in one buffer and one copy
+    std::vector<int64_t> tab;
+    tab.reserve(9 * (size_t)nk + (nk + 1) / 2);
+    for (const auto* v : {&aoff, &acnt, &nper, &jcnt, &toff, &tcnt})
+        tab.insert(tab.end(), v->begin(), v->end());
+    tab.resize(9 * (size_t)nk + (nk + 1) / 2);
+    std::memcpy(tab.data() + 6 * (size_t)nk, kpar.data(), 3 * (size_t)nk * 8);
+    std::memcpy(tab.data() + 9 * (size_t)nk, pl->h_kern_len.data(), (size_t)nk * 4);
+    DBuf<int64_t> d_tab;
+    DBuf<double> d_a;
+    MM_TRY(d_tab.alloc(tab.size()));
     MM_TRY(d_a.alloc(std::max<int64_t>(1, atot)));
     MM_TRY(d_t.alloc(ttot));
-    MM_TRY(d_aoff.alloc(nk));
-    MM_TRY(d_acnt.alloc(nk));
-    MM_TRY(d_nper.alloc(nk));
-    MM_TRY(d_jcnt.alloc(nk));
-    MM_TRY(d_toff.alloc(nk));
-    MM_TRY(d_tcnt.alloc(nk));
-    MM_HIP(hipMemcpyAsync(d_klen.p, pl->h_kern_len.data(), nk * 4, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_kpar.p, kpar.data(), 3 * nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_aoff.p, aoff.data(), nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_acnt.p, acnt.data(), nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_nper.p, nper.data(), nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_jcnt.p, jcnt.data(), nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_toff.p, toff.data(), nk * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(d_tcnt.p, tcnt.data(), nk * 8, hipMemcpyHostToDevice, st));
+    MM_HIP(hipMemcpyAsync(d_tab.p, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st));
+    const int64_t *d_aoff = d_tab.p, *d_acnt = d_aoff + nk, *d_nper = d_acnt + nk,
+                  *d_jcnt = d_nper + nk, *d_toff = d_jcnt + nk, *d_tcnt = d_toff + nk;
+    const double* d_kpar = reinterpret_cast<const double*>(d_tcnt + nk);
+    const int32_t* d_klen = reinterpret_cast<const int32_t*>(d_kpar + 3 * (size_t)nk);
     if (direct) {
         const int gx = (int)std::max<int64_t>(1, std::min<int64_t>((amax + 255) / 256, 1024));
-        hipLaunchKernelGGL(k_inv_psd, dim3(gx, nk), dim3(256), 0, st, d_klen.p, d_kpar.p,
-                           d_aoff.p, d_acnt.p, pl->opts.f_samp, d_a.p, nk, what);
+        hipLaunchKernelGGL(k_inv_psd, dim3(gx, nk), dim3(256), 0, st, d_klen, d_kpar,
+                           d_aoff, d_acnt, pl->opts.f_samp, d_a.p, nk, what);
         MM_HIP(hipGetLastError());
         const int64_t jmax = *std::max_element(jcnt.begin(), jcnt.end());
         hipLaunchKernelGGL(k_cos_transform, dim3((jmax + kCtThreads - 1) / kCtThreads, nk),
-                           dim3(kCtThreads), 0, st, d_a.p, d_aoff.p, d_acnt.p, d_nper.p, d_jcnt.p,
-                           d_toff.p, d_t.p, nk);
+                           dim3(kCtThreads), 0, st, d_a.p, d_aoff, d_acnt, d_nper, d_jcnt,
+                           d_toff, d_t.p, nk);
         MM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_taps_finish, dim3(std::max<int64_t>(1, (jmax + 255) / 256), nk),
-                           dim3(256), 0, st, d_t.p, d_toff.p, d_tcnt.p, d_klen.p, lam,
+                           dim3(256), 0, st, d_t.p, d_toff, d_tcnt, d_klen, lam,
                            pl->opts.window, nk);
         MM_HIP(hipGetLastError());
     }
@@ -1287,11 +1285,11 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
         MM_TRY(sum_rows(fft_ids, poff, d_kid, d_poff));
         MM_TRY(d_part.alloc((size_t)poff[nf] * kmax));
         hipLaunchKernelGGL((k_taps_fft<kPlanLogM, kPlanNT>), dim3(rmax, nf), dim3(kPlanNT), 0, st,
-                           d_kid.p, d_klen.p, d_kpar.p, d_tcnt.p, pl->opts.f_samp, d_tw.p, kmax,
+                           d_kid.p, d_klen, d_kpar, d_tcnt, pl->opts.f_samp, d_tw.p, kmax,
                            d_poff.p, d_part.p, what);
         MM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, nf), dim3(256), 0, st, d_kid.p,
-                           d_klen.p, d_toff.p, d_tcnt.p, d_part.p, kmax, d_poff.p, lam,
+                           d_klen, d_toff, d_tcnt, d_part.p, kmax, d_poff.p, lam,
                            pl->opts.window, d_t.p);
         MM_HIP(hipGetLastError());
     }
@@ -1323,12 +1321,12 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
                            dim3(kPlanNT), 0, st, d_clen.p, lam, d_tw.p, d_chirp.p);
         MM_HIP(hipGetLastError());
         hipLaunchKernelGGL((k_taps_czt<kPlanLogM, kPlanNT>), dim3((unsigned)seg.size()),
-                           dim3(kPlanNT), 0, st, d_seg.p, d_klen.p, d_kpar.p, lam,
+                           dim3(kPlanNT), 0, st, d_seg.p, d_klen, d_kpar, lam,
                            pl->opts.f_samp, d_tw.p, (const double2*)d_chirp.p, kmax, d_part_c.p,
                            what);
         MM_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, nf), dim3(256), 0, st, d_kid_c.p,
-                           d_klen.p, d_toff.p, d_tcnt.p, d_part_c.p, kmax, d_poff_c.p, lam,
+                           d_klen, d_toff, d_tcnt, d_part_c.p, kmax, d_poff_c.p, lam,
                            pl->opts.window, d_t.p);
         MM_HIP(hipGetLastError());
     }

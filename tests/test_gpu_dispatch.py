@@ -263,3 +263,56 @@ def test_segmented_sums_of_every_run_length(ns, dtype):
     want = np.stack([np.bincount(pix, z * c, hits.size) for c in cols], 1)
     assert np.array_equal(got, want)
     plan.close()
+
+
+def test_blocks_of_closed_plans_on_other_streams_and_threads():
+    """Plans made, used and closed in turn on the default stream and on others, from one thread
+    and from three at once: each takes over device and host blocks that the one before used a
+    moment ago, and gives the same map bit for bit."""
+    from concurrent.futures import ThreadPoolExecutor
+    scans = [synth.raster_iqu(side=s, spp=8, interval_len=s * s * 4, seed_key=95 + s, n_det=4,
+                              lam=64, fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+             for s in (23, 24)]
+    data = [torch.from_numpy(sc.noise).cuda() for sc in scans]
+    torch.cuda.synchronize()
+
+    def solve(k, stream):
+        with torch.cuda.stream(stream):
+            p = Plan.from_scan(scans[k])
+            x, info = p.pcg_solve(p.rhs(data[k]), tol=1e-9, max_iter=2000)
+            p.close()
+            x = x.cpu()
+        return x, info["history"]
+
+    default = torch.cuda.default_stream()
+    want = [solve(k, default) for k in (0, 1)]
+
+    def check(streams):
+        for i, st in enumerate(streams):
+            x, h = solve(i % 2, st)
+            assert torch.equal(x, want[i % 2][0]) and np.array_equal(h, want[i % 2][1]), i
+
+    side = [torch.cuda.Stream() for _ in range(3)]
+    check([default, side[0], side[1], default, side[0], default, default, side[1]])
+    with ThreadPoolExecutor(3) as ex:
+        list(ex.map(check, [[default, side[0], default], [side[1], default, side[1]],
+                            [side[2], side[2], default]]))
+
+
+def test_histories_of_a_batch_only_where_asked_for():
+    """One copy fetches the residuals of a batch: each problem's history is its own, of its own
+    length, and a solve without histories leaves the iterations alone."""
+    scans = [synth.raster_iqu(side=s, spp=8, interval_len=s * s * 4, seed_key=80 + s, n_det=4,
+                              lam=64, fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+             for s in (7, 14, 9)]
+    pb = _gpu_plan(scans, fft_len_f64=4096)
+    b = pb.rhs(torch.from_numpy(np.concatenate([sc.noise for sc in scans])).cuda())
+    x, info = pb.pcg_solve(b, tol=1e-9, max_iter=2000)
+    y, bare = pb.pcg_solve(b, tol=1e-9, max_iter=2000, history=False)
+    assert torch.equal(x, y)
+    for k, p in enumerate(info["problems"]):
+        assert p["history"].size == p["iterations"] > 0
+        assert p["history"][-1] <= 1e-9 < p["history"][-2]
+        assert bare["problems"][k]["iterations"] == p["iterations"]
+        assert bare["problems"][k]["history"].size == 0
+    pb.close()
