@@ -303,12 +303,6 @@ int apply_A64_sparse_i(mm_plan_t pl, const double* xi, double* y, const uint8_t*
     return scatter64(pl, pl->tod64a.p, y, nullptr);
 }
 
-int apply_A32_sparse(mm_plan_t pl, const double* x, double* y, const uint8_t* int_on) {
-    MM_TRY(pack_map32(pl, x));
-    MM_TRY(toeplitz_map32(pl, x, pl->tod32a.p, nullptr, true, int_on));
-    return scatter32(pl, pl->tod32a.p, y, nullptr);
-}
-
 int apply_A32(mm_plan_t pl, const double* x, double* y, const int* mask) {
     MM_TRY(pack_map32(pl, x));
     return apply_A32_tag(pl, x, y, mask, -1);

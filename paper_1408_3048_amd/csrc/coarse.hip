@@ -817,6 +817,29 @@ __global__ void k_zd_to_vec(const int32_t* __restrict__ lp, const TA* __restrict
         out[v0 + i] = (double)src[i];
 }
 
+// columns k0 .. k0 + gridDim.z of every problem's dense block into maps side by side, as N^-1 P
+// reads them: packed (NS = 3: [c][n_obs][4] floats) or plain doubles (NS = 1: [c][n_obs]);
+// zeros where the problem (blockIdx.y) has no such column
+template <int NS, typename TM>
+__global__ void k_zd_to_maps(const float* __restrict__ zd, const int64_t* __restrict__ ooff,
+                             const int32_t* __restrict__ ncols,
+                             const int64_t* __restrict__ blk_off, int32_t k0, int64_t n_obs,
+                             TM* __restrict__ maps) {
+    const int b = blockIdx.y, k = k0 + blockIdx.z;
+    const int64_t p0 = ooff[b], n = ooff[b + 1] - p0;
+    const bool has = k < ncols[b];
+    const float* src = zd + blk_off[b] + (has ? (int64_t)k * n * NS : 0);
+    TM* dst = maps + (int64_t)blockIdx.z * n_obs + p0;
+    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n;
+         p += (int64_t)gridDim.x * blockDim.x) {
+        if constexpr (NS == 3)
+            dst[p] = has ? make_float4(src[3 * p], src[3 * p + 1], src[3 * p + 2], 0.0f)
+                         : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        else
+            dst[p] = has ? (double)src[p] : 0.0;
+    }
+}
+
 // column-major [r][n] block -> row-major [npad][rp] FP64 (rows past n and columns past r
 // are left as they are: zeroed by the caller); tiles of 64 entries x 64 columns (columns
 // 64 blockIdx.y + ...) go through LDS, so that reads and writes are both coalesced
@@ -1860,16 +1883,52 @@ int build_coarse_dense(mm_plan_t pl, const double* basis, int64_t basis_stride,
         }
         MM_HIP(hipStreamSynchronize(st));
     }
-    // AZ_D, one A application per column index over all problems
-    {
-        DBuf<int64_t> dzoff;
+    // AZ_D: one A application per column index over all problems; mixed plans take kAzGroup
+    // columns at a time, as the A Z_S build does (at 2^20 samples a column alone takes five
+    // launches of 3-15 us, which leave the chip half idle: 43 columns 2.1 -> 0.4 ms)
+    DBuf<int64_t> dzoff;
+    MM_TRY(dzoff.alloc(B + 1));
+    MM_HIP(hipMemcpyAsync(dzoff.p, zoff.data(), (B + 1) * 8, hipMemcpyHostToDevice, st));
+    if (mixed) {
+        DBuf<int32_t> d_rb;
+        DBuf<float> maps, todg;
+        const int cg = std::min<int32_t>(kAzGroup, r_max);
+        // 4 floats a pixel, or one double
+        MM_TRY(maps.alloc((size_t)cg * pl->n_obs * (ns == 3 ? 4 : 2)));
+        MM_TRY(todg.alloc((size_t)cg * pl->n_t));
+        MM_TRY(d_rb.alloc(B));
+        MM_HIP(hipMemcpyAsync(d_rb.p, rb.data(), B * 4, hipMemcpyHostToDevice, st));
+        int64_t np_max = 1;
+        for (int b = 0; b < B; ++b) np_max = std::max<int64_t>(np_max, oo[b + 1] - oo[b]);
+        const unsigned gx = (unsigned)std::min<int64_t>(1024, (np_max + 255) / 256);
+        for (int32_t k0 = 0; k0 < r_max; k0 += kAzGroup) {
+            const int nc = std::min<int32_t>(kAzGroup, r_max - k0);
+            const dim3 g(gx, B, nc);
+            if (ns == 3) {
+                hipLaunchKernelGGL((k_zd_to_maps<3, float4>), g, dim3(256), 0, st, zd32.p,
+                                   pl->ooff.p, d_rb.p, dzoff.p, k0, pl->n_obs, (float4*)maps.p);
+                MM_HIP(hipGetLastError());
+                MM_TRY(toeplitz_map32_layers(pl, nullptr, 0, maps.p, 4 * pl->n_obs, todg.p,
+                                             pl->n_t, nullptr, 0, nc));
+            } else {
+                hipLaunchKernelGGL((k_zd_to_maps<1, double>), g, dim3(256), 0, st, zd32.p,
+                                   pl->ooff.p, d_rb.p, dzoff.p, k0, pl->n_obs, (double*)maps.p);
+                MM_HIP(hipGetLastError());
+                MM_TRY(toeplitz_map32_layers(pl, (const double*)maps.p, pl->n_obs, nullptr, 0,
+                                             todg.p, pl->n_t, nullptr, 0, nc));
+            }
+            for (int c = 0; c < nc; c += kScatterCols)
+                MM_TRY(scatter_cols32(pl, todg.p + c * pl->n_t, pl->n_t,
+                                      std::min(kScatterCols, nc - c), k0 + c, d_rb.p, dzoff.p,
+                                      az32.p));
+        }
+        MM_HIP(hipStreamSynchronize(st));
+    } else {
         DBuf<int32_t> lprob;
         DBuf<double> x, y;
-        MM_TRY(dzoff.alloc(B + 1));
         MM_TRY(lprob.alloc((size_t)r_max * B));
         MM_TRY(x.alloc(nv));
         MM_TRY(y.alloc(nv));
-        MM_HIP(hipMemcpyAsync(dzoff.p, zoff.data(), (B + 1) * 8, hipMemcpyHostToDevice, st));
         std::vector<int32_t> hp;
         std::vector<int32_t> lcnt(r_max, 0);
         for (int32_t k = 0; k < r_max; ++k)
@@ -1886,25 +1945,14 @@ int build_coarse_dense(mm_plan_t pl, const double* basis, int64_t basis_stride,
         for (int32_t k = 0; k < r_max; ++k) {
             const dim3 g(sgx, lcnt[k]);
             MM_HIP(hipMemsetAsync(x.p, 0, nv * 8, st));
-            if (mixed) {
-                hipLaunchKernelGGL(k_zd_to_vec<float>, g, dim3(256), 0, st, lprob.p + lo,
-                                   (const float*)zd32.p, pl->ooff.p, (int)ns,
-                                   (const int64_t*)dzoff.p, k, x.p);
-                MM_HIP(hipGetLastError());
-                MM_TRY(apply_A32_sparse(pl, x.p, y.p));
-                hipLaunchKernelGGL(k_store_az<float>, g, dim3(256), 0, st, lprob.p + lo,
-                                   (const double*)y.p, pl->ooff.p, (int)ns,
-                                   (const int64_t*)dzoff.p, k, az32.p);
-            } else {
-                hipLaunchKernelGGL(k_zd_to_vec<double>, g, dim3(256), 0, st, lprob.p + lo,
-                                   (const double*)zd64.p, pl->ooff.p, (int)ns,
-                                   (const int64_t*)dzoff.p, k, x.p);
-                MM_HIP(hipGetLastError());
-                MM_TRY(apply_A64_sparse(pl, x.p, y.p));
-                hipLaunchKernelGGL(k_store_az<double>, g, dim3(256), 0, st, lprob.p + lo,
-                                   (const double*)y.p, pl->ooff.p, (int)ns,
-                                   (const int64_t*)dzoff.p, k, az64.p);
-            }
+            hipLaunchKernelGGL(k_zd_to_vec<double>, g, dim3(256), 0, st, lprob.p + lo,
+                               (const double*)zd64.p, pl->ooff.p, (int)ns,
+                               (const int64_t*)dzoff.p, k, x.p);
+            MM_HIP(hipGetLastError());
+            MM_TRY(apply_A64_sparse(pl, x.p, y.p));
+            hipLaunchKernelGGL(k_store_az<double>, g, dim3(256), 0, st, lprob.p + lo,
+                               (const double*)y.p, pl->ooff.p, (int)ns,
+                               (const int64_t*)dzoff.p, k, az64.p);
             MM_HIP(hipGetLastError());
             lo += lcnt[k];
         }

@@ -374,8 +374,7 @@ int pack_map64(mm_plan_t pl, const double* x);
 int pack_map32(mm_plan_t pl, const double* x);
 int toeplitz_map64(mm_plan_t pl, const double* x, double* z, const int* mask,
                    bool skip_zero = false, const uint8_t* int_on = nullptr);
-int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask,
-                   bool skip_zero = false, const uint8_t* int_on = nullptr);
+int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask);
 // zero-skipping N^-1 P of a map whose Q and U rows are zero (or of an I-only plan's map),
 // given by its I rows xi (n_obs values): no weights are read; int_on as above
 int toeplitz_map64_i(mm_plan_t pl, const double* xi, double* z, const uint8_t* int_on);
@@ -478,7 +477,6 @@ int apply_A32(mm_plan_t pl, const double* x, double* y, const int* mask);
 // A x for mostly-zero x (the coarse-space columns): all-zero tiles skip the transform;
 // int_on (optional): per-interval flags, 0 where P x vanishes on the whole interval
 int apply_A64_sparse(mm_plan_t pl, const double* x, double* y, const uint8_t* int_on = nullptr);
-int apply_A32_sparse(mm_plan_t pl, const double* x, double* y, const uint8_t* int_on = nullptr);
 // the same for a map whose Q and U rows are zero, given by its I rows xi (n_obs values)
 int apply_A64_sparse_i(mm_plan_t pl, const double* xi, double* y, const uint8_t* int_on);
 

@@ -1645,11 +1645,8 @@ int toeplitz_map64_i(mm_plan_t pl, const double* xi, double* z, const uint8_t* i
     return launch<double>(a, pl->fft64, pl->stream);
 }
 
-int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask, bool skip_zero,
-                   const uint8_t* int_on) {
+int toeplitz_map32(mm_plan_t pl, const double* x, float* z, const int* mask) {
     auto a = base_args<float>(pl, pl->fft32);
-    a.skip_zero = skip_zero;
-    a.int_on = skip_zero ? int_on : nullptr;
     a.x = x;
     if (pl->n_s == 3) a.xp = pl->xp32.p;
     a.mode = pl->n_s == 3 ? 0 : 1;

@@ -316,3 +316,42 @@ def test_histories_of_a_batch_only_where_asked_for():
         assert bare["problems"][k]["iterations"] == p["iterations"]
         assert bare["problems"][k]["history"].size == 0
     pb.close()
+
+
+@pytest.mark.parametrize("ns", [1, 3])
+@pytest.mark.parametrize("max_cols", [1, 8, 19])
+def test_dense_coarse_columns_in_groups(max_cols, ns):
+    """A Z_D of a mixed plan is formed 8 columns at a time over the problems of a batch, whose
+    column counts differ: E = Z^T A Z of every problem against A applied to one column of each
+    problem after the other.  The bar is the rounding of A Z to 32 bits."""
+    scans = [synth.raster_iqu(side=s, spp=8, interval_len=s * s * 4, seed_key=60 + s, n_det=4,
+                              lam=64, fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+             for s in (23, 12, 31)]
+    pix = np.concatenate([sc.pix + i * 1024 for i, sc in enumerate(scans)]).astype(np.int32)
+    w = torch.from_numpy(np.concatenate([sc.weights for sc in scans])).cuda()
+    off = np.cumsum([0] + [int(k) for sc in scans for k in np.diff(sc.offsets)])
+    psd = np.concatenate([np.stack([sc.sigma, sc.fknee, sc.alpha], 1) for sc in scans])
+    prob = np.cumsum([0] + [sc.n_intervals for sc in scans])
+    p = Plan(torch.from_numpy(pix).cuda(), w if ns == 3 else None, 3 * 1024, off, psd,
+             n_stokes=ns, lam=64, f_samp=scans[0].f_samp, problem_intervals=prob,
+             precision="mixed", coarse=True, fft_len_f64=4096, fft_len_f32=4096)
+    b = p.rhs(torch.from_numpy(np.concatenate([sc.noise for sc in scans])).cuda())
+    p.coarse_from_krylov(b, tol=1e-9, max_iter=2000, eps_tol=1.5, max_cols=max_cols)
+    Z, E, po = p.dense_columns(), p.coarse_matrix(), p.problem_pixels() * ns
+    assert max(z.shape[0] for z in Z) == max_cols
+    AZ = [torch.zeros_like(z) for z in Z]
+    for k in range(max_cols):
+        x = torch.zeros(p.n_vec, dtype=torch.float64, device="cuda")
+        for i, z in enumerate(Z):
+            if k < z.shape[0]:
+                x[po[i]:po[i + 1]] = z[k]
+        y = p.apply_A(x, precision="mixed")
+        for i, z in enumerate(Z):
+            if k < z.shape[0]:
+                AZ[i][k] = y[po[i]:po[i + 1]]
+    for z, az, e in zip(Z, AZ, E):
+        z, az = z.cpu().numpy(), az.cpu().numpy()
+        ref = 0.5 * (z @ az.T + az @ z.T)
+        bar = 2.0 ** -23 * np.linalg.norm(z, axis=1)[:, None] * np.linalg.norm(az, axis=1)[None]
+        assert (np.abs(e - ref) <= np.maximum(bar, bar.T)).all()
+    p.close()
