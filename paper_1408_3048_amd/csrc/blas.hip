@@ -316,12 +316,9 @@ __global__ __launch_bounds__(kVecThreads) void k_pcg_final(PcgCtl c) {
 
 int64_t nvec(mm_plan_t pl) { return pl->n_obs * pl->n_s; }
 
-// interval -> problem map and the block offsets of the per-problem vector kernels
+// block offsets of the per-problem vector kernels
 int build_batch_layout(mm_plan_t pl) {
     const int B = pl->n_prob;
-    std::vector<int32_t> ip(pl->n_int);
-    for (int b = 0; b < B; ++b)
-        for (int32_t j = pl->h_pint[b]; j < pl->h_pint[b + 1]; ++j) ip[j] = b;
     std::vector<int32_t> eb(B + 1, 0), pb(B + 1, 0);
     for (int b = 0; b < B; ++b) {
         const int64_t np = pl->h_ooff[b + 1] - pl->h_ooff[b];
@@ -340,10 +337,8 @@ int build_batch_layout(mm_plan_t pl) {
     pl->n_eblk = eb[B];
     pl->n_pblk = pb[B];
     hipStream_t st = pl->stream;
-    MM_TRY(pl->int_prob.alloc(pl->n_int));
     MM_TRY(pl->eblk.alloc(B + 1));
     MM_TRY(pl->pblk.alloc(B + 1));
-    MM_HIP(hipMemcpyAsync(pl->int_prob.p, ip.data(), ip.size() * 4, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(pl->eblk.p, eb.data(), (B + 1) * 4, hipMemcpyHostToDevice, st));
     MM_HIP(hipMemcpyAsync(pl->pblk.p, pb.data(), (B + 1) * 4, hipMemcpyHostToDevice, st));
     MM_HIP(hipStreamSynchronize(st));

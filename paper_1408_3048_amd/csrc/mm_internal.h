@@ -75,6 +75,15 @@ struct DBuf {
     DBuf& operator=(const DBuf&) = delete;
 };
 
+// An overlap-save tile: len outputs from sample `out`, of interval `inter` = [lo, hi) with
+// kernel `kern`, of problem `prob`.  One aligned record: a workgroup has all of it after one
+// scalar load, where looking the interval up first took three loads in a row.
+struct alignas(16) TileRec {
+    int64_t out, lo, hi;
+    int32_t len, inter, kern, prob;
+    int64_t pad;
+};
+
 // ---------------------------------------------------------------- overlap-save tiling
 // One FFT configuration (per precision): tiles of L_max outputs read a window of
 // L + 2 lambda samples into a real buffer of n_r = 2^(logm+1) points.
@@ -98,9 +107,7 @@ struct FftTiling {
     bool paired = false;     // tiles 2p and 2p + 1, of one interval, go through one transform of
                              // n_r complex points (the second may be empty)
     int64_t n_tiles = 0;
-    DBuf<int64_t> tile_out;  // first output sample of every tile
-    DBuf<int32_t> tile_len;  // outputs of every tile
-    DBuf<int32_t> tile_int;  // interval of every tile
+    DBuf<TileRec> tiles;     // [n_tiles]
     DBuf<double> H64;        // [n_kern][M+1] kernel spectrum / n_r, FP64 operator; paired:
                              // [n_kern][n_r] in the order of k_toeplitz_pair
     DBuf<float> H32;         // same, FP32 operator
@@ -245,7 +252,6 @@ struct mm_plan_s {
     std::vector<int64_t> h_pn;          // [B] samples of every problem
     int64_t pt_range = 512;             // samples per P^T work range
     int64_t n_sorted = 0;               // padded sorted length (problems start 8-aligned)
-    mm::DBuf<int32_t> int_prob;         // [n_int] problem of every interval
     mm::DBuf<int64_t> ooff;             // [B+1] compact pixel offsets
     mm::DBuf<int32_t> eblk, pblk;       // [B+1] vector-kernel block offsets (elements, pixels)
     int32_t n_eblk = 0, n_pblk = 0;     // grid sizes of the vector kernels

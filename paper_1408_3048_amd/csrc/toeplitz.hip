@@ -194,16 +194,10 @@ struct ToepArgs {
     T* z;
     const T* H;           // [n_kern][M + 1]
     const T* tw;          // [M][2]
-    const int64_t* tile_out;
-    const int32_t* tile_len;
-    const int32_t* tile_int;
-    const int64_t* int_lo;
-    const int64_t* int_hi;
-    const int32_t* int_kern;
+    const TileRec* tiles;
     int lam;
     int64_t n_tiles;          // tiles of the launch (blocks are mapped to tiles XCD-major)
     const int* mask;          // per-problem flags: tiles of problems with mask 0 are skipped
-    const int32_t* int_prob;  // problem of every interval
     int skip_zero;            // map modes: all-zero windows skip the transform
     const uint8_t* int_on;    // zero-skipping launches: intervals flagged 0 have an all-zero
                               // input (known beforehand) and write zeros without loading it
@@ -235,35 +229,42 @@ __device__ __forceinline__ void spectrum_pair(T hk, T hm, T c, T s, T zkr, T zki
     wmi = am * zmi + g * zkr;
 }
 
-// spectrum product on pairs (k, M - k) of the bit-reversed half-length transform.  A
-// thread's kernel-spectrum and twiddle values for all its pairs are loaded before the
-// first product, so their memory latency is paid once, not once per pair.
+// A thread's kernel-spectrum and twiddle values for the pairs k = tid + i NT <= M/2 of the
+// spectrum product, loaded together, so that their memory latency is paid once, not once per
+// pair.
 template <typename T, int LOGM, int NT>
-__device__ __forceinline__ void spectrum_pass(const CBuf<T>& buf, const T* __restrict__ H,
-                                              const T* __restrict__ tw) {
-    constexpr int M = 1 << LOGM;
-    constexpr int NI = (M / 2 + NT) / NT;  // pairs k = tid + i NT <= M/2
+struct SpectrumValues {
+    static constexpr int M = 1 << LOGM, NI = (M / 2 + NT) / NT;
     T hk[NI], hm[NI], cc[NI], ss[NI];
+    __device__ __forceinline__ SpectrumValues(const T* __restrict__ H, const T* __restrict__ tw) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int k0 = threadIdx.x + i * NT;
-        const int k = k0 <= M / 2 ? k0 : M / 2;  // valid address; not used past M/2
-        hk[i] = H[k];
-        hm[i] = H[M - k];
-        cc[i] = tw[2 * k];
-        ss[i] = -tw[2 * k + 1];
+        for (int i = 0; i < NI; ++i) {
+            const int k0 = threadIdx.x + i * NT;
+            const int k = k0 <= M / 2 ? k0 : M / 2;  // valid address; not used past M/2
+            hk[i] = H[k];
+            hm[i] = H[M - k];
+            cc[i] = tw[2 * k];
+            ss[i] = -tw[2 * k + 1];
+        }
     }
+};
+
+// spectrum product on pairs (k, M - k) of the bit-reversed half-length transform
+template <typename T, int LOGM, int NT>
+__device__ __forceinline__ void spectrum_pass(const CBuf<T>& buf,
+                                              const SpectrumValues<T, LOGM, NT>& s) {
+    constexpr int M = 1 << LOGM, NI = SpectrumValues<T, LOGM, NT>::NI;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int k = threadIdx.x + i * NT;
-        if (k > M / 2) break;
+        if (i == NI - 1 && k > M / 2) continue;  // only the last can be past M/2
         const int km = M - k;
         const int ak = rev_bits<LOGM>(k);
         const int am = k == 0 ? ak : rev_bits<LOGM>(km);  // bin M is bin 0
         T zkr, zki, zmr, zmi, wkr, wki, wmr, wmi;
         buf.get(ak, zkr, zki);
         buf.get(am, zmr, zmi);
-        spectrum_pair(hk[i], hm[i], cc[i], ss[i], zkr, zki, zmr, zmi, wkr, wki, wmr, wmi);
+        spectrum_pair(s.hk[i], s.hm[i], s.cc[i], s.ss[i], zkr, zki, zmr, zmi, wkr, wki, wmr, wmi);
         buf.put(ak, wkr, wki);
         if (k != 0 && km != k) buf.put(am, wmr, wmi);
     }
@@ -481,26 +482,19 @@ __device__ __forceinline__ bool load_window(const ToepArgs<T>& a, const CBuf<T>&
 // waves per SIMD that the tile's LDS allows (160 KB per CU, 4 SIMDs per CU), capped where
 // the butterflies and gathers would spill (4 waves = 128 VGPRs for FP32, 3 = 170
 // for FP64): the register budget the compiler must meet so that LDS bounds occupancy
-// the LDS twiddle table of the passes after the first is used where it leaves the tile's
-// occupancy (blocks per CU, by LDS and by the 32 waves a CU holds) unchanged
 template <typename T, int LOGM, int NT>
-constexpr bool ltw_enabled() {
+constexpr int tile_waves_per_simd(int table_bytes = 0) {
     constexpr int bytes = 2 * (1 << LOGM) * (int)sizeof(T);
-    constexpr int tbytes = 2 * ltw_total(LOGM) * (int)sizeof(T);
-    constexpr int wmax = 32 / (NT / 64);
-    constexpr int b0 = (160 * 1024) / bytes < wmax ? (160 * 1024) / bytes : wmax;
-    constexpr int b1 = (160 * 1024) / (bytes + tbytes) < wmax ? (160 * 1024) / (bytes + tbytes)
-                                                              : wmax;
-    return ltw_total(LOGM) > 0 && b0 == b1;
-}
-
-template <typename T, int LOGM, int NT>
-constexpr int tile_waves_per_simd() {
-    constexpr int bytes = 2 * (1 << LOGM) * (int)sizeof(T);
-    constexpr int blocks = (160 * 1024) / bytes;
-    constexpr int w = blocks * (NT / 64) / 4;
+    const int w = (160 * 1024) / (bytes + table_bytes) * (NT / 64) / 4;
     constexpr int cap = sizeof(T) == 4 ? 4 : 3;
     return w < 1 ? 1 : (w > cap ? cap : w);
+}
+// the LDS twiddle table is used where it leaves the tile's occupancy unchanged
+template <typename T, int LOGM, int NT>
+constexpr bool ltw_enabled() {
+    return ltw_total(LOGM) > 0 &&
+           tile_waves_per_simd<T, LOGM, NT>(2 * ltw_total(LOGM) * (int)sizeof(T)) ==
+               tile_waves_per_simd<T, LOGM, NT>();
 }
 
 // threads of a tile: one radix-16 group per thread and pass
@@ -509,6 +503,11 @@ constexpr int tile_threads() {
     constexpr int nt = (1 << LOGM) / 16;
     return nt > 1024 ? 1024 : (nt < 256 ? 256 : nt);
 }
+
+struct Unused {
+    template <class... A>
+    __device__ __forceinline__ explicit Unused(const A&...) {}
+};
 
 // SKIPZ: a tile whose input window is all zero writes zeros and skips the transform (the
 // exact result; used for the sparse A Z columns; costs a block vote in LDS)
@@ -535,14 +534,13 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
     // column are neighbours and would all land on one XCD
     const int64_t tile = SKIPZ ? (int64_t)blockIdx.x : xcd_item(blockIdx.x, a.n_tiles);
     if (tile < 0 || tile >= a.n_tiles) return;
-    const int j = a.tile_int[tile];
-    if (a.mask && !a.mask[a.int_prob[j]]) return;
-    const int64_t o = a.tile_out[tile];
-    const int L = a.tile_len[tile];
-    const int64_t lo = a.int_lo[j], hi = a.int_hi[j];
+    const TileRec tr = a.tiles[tile];
+    if (a.mask && !a.mask[tr.prob]) return;
+    const int64_t o = tr.out, lo = tr.lo, hi = tr.hi;
+    const int L = tr.len;
     const int lam = a.lam;
     if constexpr (SKIPZ) {
-        if (a.int_on && !a.int_on[j]) {
+        if (a.int_on && !a.int_on[tr.inter]) {
             for (int i = threadIdx.x; i < L; i += NT) a.z[o + i] = (T)0;
             return;
         }
@@ -550,6 +548,12 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
     // the twiddle table is ordered by the barrier after the load (zero-skipping launches:
     // filled only for non-zero windows, behind a barrier of its own)
     if constexpr (LTW && !SKIPZ) fill_ltw<T, LOGM, NT>(a.tw, lt);
+    // the shortest tiles, a launch of which is a chain of latencies, have registers to load the
+    // spectrum's values with the window (with the tile in one record, N^-1 P of 2^14 samples
+    // 9.5 -> 8.9 us; the record alone, 2^20 samples FP32 14.7 -> 13.9 and FP64 24.8 -> 24.3)
+    constexpr bool EARLY = LOGM == 10;
+    [[maybe_unused]] std::conditional_t<EARLY, SpectrumValues<T, LOGM, NT>, Unused> early(
+        a.H + (int64_t)tr.kern * (M + 1), a.tw);
     const bool nz = load_window<T, LOGM, NT, MODE>(a, buf, o - lam, L + 2 * lam, lo, hi);
     if constexpr (SKIPZ) {
         if (!__syncthreads_or(nz)) {  // zero window: the exact result is zero
@@ -566,11 +570,16 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
     }
     if constexpr (LOGM % 4 == 1) {  // the radix-2 stages go into the spectrum pass
         fwd_passes<T, LOGM, NT, LOGM, 1, LTW>(buf, a.tw, lt);
-        spectrum_pass_r2<T, LOGM, NT>(buf, a.H + (int64_t)a.int_kern[j] * (M + 1), a.tw);
+        spectrum_pass_r2<T, LOGM, NT>(buf, a.H + (int64_t)tr.kern * (M + 1), a.tw);
         inv_passes<T, LOGM, NT, LOGM, 1, LTW>(buf, a.tw, lt);
+    } else if constexpr (EARLY) {
+        fwd_passes<T, LOGM, NT, LOGM, 0, LTW>(buf, a.tw, lt);
+        spectrum_pass<T, LOGM, NT>(buf, early);
+        inv_passes<T, LOGM, NT, LOGM, 0, LTW>(buf, a.tw, lt);
     } else {
         fwd_passes<T, LOGM, NT, LOGM, 0, LTW>(buf, a.tw, lt);
-        spectrum_pass<T, LOGM, NT>(buf, a.H + (int64_t)a.int_kern[j] * (M + 1), a.tw);
+        spectrum_pass<T, LOGM, NT>(
+            buf, SpectrumValues<T, LOGM, NT>(a.H + (int64_t)tr.kern * (M + 1), a.tw));
         inv_passes<T, LOGM, NT, LOGM, 0, LTW>(buf, a.tw, lt);
     }
     T* zo = a.z + o;  // block-uniform base, 32-bit offsets
@@ -700,14 +709,14 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
     __shared__ __align__(16) double s[F::ELEMS];
     const int64_t pair = SKIPZ ? (int64_t)blockIdx.x : xcd_item(blockIdx.x, a.n_tiles);
     if (pair < 0 || pair >= a.n_tiles) return;
-    const int j = a.tile_int[2 * pair];
-    if (a.mask && !a.mask[a.int_prob[j]]) return;
-    const int64_t o[2] = {a.tile_out[2 * pair], a.tile_out[2 * pair + 1]};
-    const int L[2] = {a.tile_len[2 * pair], a.tile_len[2 * pair + 1]};  // L[1] may be 0
-    const int64_t lo = a.int_lo[j], hi = a.int_hi[j];
+    const TileRec tr = a.tiles[2 * pair];
+    const int64_t o[2] = {tr.out, a.tiles[2 * pair + 1].out};
+    const int L[2] = {tr.len, a.tiles[2 * pair + 1].len};  // L[1] may be 0
+    if (a.mask && !a.mask[tr.prob]) return;
+    const int64_t lo = tr.lo, hi = tr.hi;
     const int lam = a.lam, t = threadIdx.x;
     if constexpr (SKIPZ) {
-        if (a.int_on && !a.int_on[j]) {
+        if (a.int_on && !a.int_on[tr.inter]) {
 #pragma unroll
             for (int w = 0; w < 2; ++w)
                 for (int i = t; i < L[w]; i += NT) a.z[o[w] + i] = 0.0;
@@ -759,7 +768,7 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
     if (go) {
         F::forward(vr, vi, s, a.tw, t);
         F::pin(vr, vi);
-        const double2* h = reinterpret_cast<const double2*>(a.H + (int64_t)a.int_kern[j] * F::N);
+        const double2* h = reinterpret_cast<const double2*>(a.H + (int64_t)tr.kern * F::N);
 #pragma unroll
         for (int q = 0; q < R / 2; ++q) {
             const double2 hv = h[q * NT + t];
@@ -1122,13 +1131,7 @@ template <typename T>
 ToepArgs<T> base_args(mm_plan_t pl, const FftTiling& ft) {
     ToepArgs<T> a{};
     a.cid = pl->cid.p;
-    a.tile_out = ft.tile_out.p;
-    a.tile_len = ft.tile_len.p;
-    a.tile_int = ft.tile_int.p;
-    a.int_lo = pl->int_lo.p;
-    a.int_hi = pl->int_hi.p;
-    a.int_kern = pl->int_kern.p;
-    a.int_prob = pl->int_prob.p;
+    a.tiles = ft.tiles.p;
     a.lam = pl->opts.lambda;
     if constexpr (sizeof(T) == 8) {
         a.H = ft.H64.p;
@@ -1471,34 +1474,27 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
     const int M = 1 << logm;
     const int64_t lmax = (int64_t)ft.n_r - 2 * (int64_t)lam;
     // balanced tiles per interval
-    std::vector<int64_t> tout;
-    std::vector<int32_t> tlen, tint;
+    std::vector<TileRec> tiles;
+    int32_t prob = 0;
     for (int32_t j = 0; j < pl->n_int; ++j) {
         const int64_t a = pl->h_off[j], b = pl->h_off[j + 1], n = b - a;
+        while (j >= pl->h_pint[prob + 1]) ++prob;
         const int64_t nt = tiles_of(n, lmax, ft.paired);
         const int64_t len = (n + nt - 1) / nt;
         for (int64_t i = 0; i < nt; ++i) {
             const int64_t s = a + i * len;
             const int64_t e = std::min(b, s + len);
-            if (e <= s) {
-                if (!ft.paired || i % 2 == 0) break;
-                tout.push_back(tout.back());  // an empty second tile
-                tlen.push_back(0);
-                tint.push_back(j);
-                break;
-            }
-            tout.push_back(s);
-            tlen.push_back((int32_t)(e - s));
-            tint.push_back(j);
+            if (e <= s && (!ft.paired || i % 2 == 0)) break;
+            // (the second tile of a pair may be empty)
+            tiles.push_back({e > s ? s : tiles.back().out, a, b, (int32_t)std::max<int64_t>(e - s, 0),
+                             j, pl->h_int_kern[j], prob, 0});
+            if (e <= s) break;
         }
     }
-    ft.n_tiles = (int64_t)tout.size();
-    MM_TRY(ft.tile_out.alloc(ft.n_tiles));
-    MM_TRY(ft.tile_len.alloc(ft.n_tiles));
-    MM_TRY(ft.tile_int.alloc(ft.n_tiles));
-    MM_HIP(hipMemcpyAsync(ft.tile_out.p, tout.data(), ft.n_tiles * 8, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(ft.tile_len.p, tlen.data(), ft.n_tiles * 4, hipMemcpyHostToDevice, st));
-    MM_HIP(hipMemcpyAsync(ft.tile_int.p, tint.data(), ft.n_tiles * 4, hipMemcpyHostToDevice, st));
+    ft.n_tiles = (int64_t)tiles.size();
+    MM_TRY(ft.tiles.alloc(ft.n_tiles));
+    MM_HIP(hipMemcpyAsync(ft.tiles.p, tiles.data(), ft.n_tiles * sizeof(TileRec),
+                          hipMemcpyHostToDevice, st));
     // twiddles exp(-2 pi i q / n_r), q < M, in FP64 (the spectra below and unpaired FP64
     // tiles) and FP32 for FP32 tiles; pairs have a table of their own
     DBuf<double> d_tw;
@@ -1709,9 +1705,7 @@ void swap_tiling(FftTiling& a, FftTiling& b) {
     std::swap(a.n_r, b.n_r);
     std::swap(a.n_tiles, b.n_tiles);
     std::swap(a.paired, b.paired);
-    a.tile_out.swap(b.tile_out);
-    a.tile_len.swap(b.tile_len);
-    a.tile_int.swap(b.tile_int);
+    a.tiles.swap(b.tiles);
     a.H64.swap(b.H64);
     a.H32.swap(b.H32);
     a.tw64.swap(b.tw64);
