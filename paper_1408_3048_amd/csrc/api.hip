@@ -269,21 +269,23 @@ void prof_invalidate(mm_plan_t pl, const size_t* mark, int first_skipped) {
 }
 
 // y = A x of the map whose packed form is already in xp64 / xp32
-static int apply_A64_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag) {
+static int apply_A64_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag,
+                         bool dot = false) {
     MM_TRY(prof_begin(pl, MM_K_NINV64, tag));
     MM_TRY(toeplitz_map64(pl, x, pl->tod64a.p, mask));
     MM_TRY(prof_end(pl, MM_K_NINV64));
     MM_TRY(prof_begin(pl, MM_K_PT64, tag));
-    MM_TRY(scatter64(pl, pl->tod64a.p, y, mask));
+    MM_TRY(scatter64(pl, pl->tod64a.p, y, mask, dot ? x : nullptr));
     return prof_end(pl, MM_K_PT64);
 }
 
-static int apply_A32_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag) {
+static int apply_A32_tag(mm_plan_t pl, const double* x, double* y, const int* mask, int tag,
+                         bool dot = false) {
     MM_TRY(prof_begin(pl, MM_K_NINV32, tag));
     MM_TRY(toeplitz_map32(pl, x, pl->tod32a.p, mask));
     MM_TRY(prof_end(pl, MM_K_NINV32));
     MM_TRY(prof_begin(pl, MM_K_PT32, tag));
-    MM_TRY(scatter32(pl, pl->tod32a.p, y, mask));
+    MM_TRY(scatter32(pl, pl->tod32a.p, y, mask, dot ? x : nullptr));
     return prof_end(pl, MM_K_PT32);
 }
 
@@ -399,9 +401,12 @@ int full_iteration(mm_plan_t pl, const EngineArgs& ea, double* x, double* r, dou
     c.replace = ea.replace;
     c.replace_ratio = ea.replace_ratio;
     c.max_iter = ea.max_iter;
-    MM_TRY(ea.op32 ? apply_A32_tag(pl, p, q, c.mask, tag) : apply_A64_tag(pl, p, q, c.mask, tag));
+    // P^T leaves the partials of p^T q of the problems whose ranges have slots
+    MM_TRY(ea.op32 ? apply_A32_tag(pl, p, q, c.mask, tag, true)
+                   : apply_A64_tag(pl, p, q, c.mask, tag, true));
     MM_TRY(prof_begin(pl, MM_K_VEC, tag));
-    MM_TRY(vec_dot(pl, p, q, kSlotPQ, c));
+    if (pl->n_slotted < pl->n_prob)
+        MM_TRY(vec_dot(pl, p, q, kSlotPQ, c, pl->n_slotted > 0 ? pl->wave_off.p : nullptr));
     if (ea.pc == MM_BJ) {
         MM_TRY(prof_end(pl, MM_K_VEC));
         MM_TRY(prof_begin(pl, MM_K_PRECOND, tag));

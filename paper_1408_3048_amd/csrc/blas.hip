@@ -18,10 +18,13 @@ __device__ __forceinline__ bool first_thread(const VecBlock& v) {
 // partials of a^T b (per problem) into `slot`
 __global__ __launch_bounds__(kVecThreads) void k_dot(const double* __restrict__ a,
                                                      const double* __restrict__ b, int slot,
-                                                     int ns, PcgCtl c) {
+                                                     int ns, PcgCtl c,
+                                                     const int64_t* __restrict__ wave_off) {
     __shared__ double red[kVecThreads];
     const VecBlock v = vec_block(c, ns, true);
     if (c.mask && !c.mask[v.b]) return;
+    // the problems whose partials P^T has left already
+    if (wave_off && wave_off[v.b + 1] - wave_off[v.b] <= kVecBlocks) return;
     double acc = 0.0;
     for (int64_t i = (int64_t)v.k * kVecThreads + threadIdx.x; i < v.n;
          i += v.stride)
@@ -367,9 +370,10 @@ PcgCtl batch_ctl(mm_plan_t pl) {
     return c;
 }
 
-int vec_dot(mm_plan_t pl, const double* a, const double* b, int slot, const PcgCtl& ctl) {
+int vec_dot(mm_plan_t pl, const double* a, const double* b, int slot, const PcgCtl& ctl,
+            const int64_t* wave_off) {
     hipLaunchKernelGGL(k_dot, dim3(pl->n_eblk), dim3(kVecThreads), 0, pl->stream, a, b, slot,
-                       pl->n_s, ctl);
+                       pl->n_s, ctl, wave_off);
     MM_HIP(hipGetLastError());
     return MM_OK;
 }

@@ -150,7 +150,7 @@ struct alignas(32) WaveRange {
     int64_t i0, i1;
     int32_t p0, p1;
     int32_t prob;
-    int32_t pad;
+    int32_t slot;  // index within the problem's ranges, or -1 where they are more than kVecBlocks
 };
 
 // Control block of the PCG kernels (passed by value).  A batch of B independent problems
@@ -278,6 +278,7 @@ struct mm_plan_s {
                                         // pixel c holds [seg[c], seg[c] + hits[c])
     mm::DBuf<uint64_t> heads;           // segment-start bit per sorted sample
     mm::DBuf<mm::WaveRange> wave_rng;   // [n_waves] work ranges of P^T
+    int32_t n_slotted = 0;              // problems whose ranges have slots for partials
     mm::DBuf<int64_t> wave_off;         // [B+1] first P^T wave of every problem
     mm::DBuf<int64_t> soff;             // [B+1] h_soff on the device
     int64_t n_waves = 0;
@@ -408,8 +409,12 @@ int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves = 0);
 // the P^T range: opts.pt_range, else the fastest candidate (autotune) or the default
 int tune_pt_range(mm_plan_t pl);
 // x = P^T z for the problems in mask
-int scatter64(mm_plan_t pl, const double* z, double* x, const int* mask);
-int scatter32(mm_plan_t pl, const float* z, double* x, const int* mask);
+// dot: also the partials of dot^T x into kSlotPQ, one per range, for the problems whose ranges
+// have slots
+int scatter64(mm_plan_t pl, const double* z, double* x, const int* mask,
+              const double* dot = nullptr);
+int scatter32(mm_plan_t pl, const float* z, double* x, const int* mask,
+              const double* dot = nullptr);
 // P^T of nc <= kScatterCols FP32 time streams z + k zstride into columns k0 + k of the
 // per-problem FP32 blocks of az (block b at blk_off[b], column-major [ncols[b]][n_vec_b]);
 // columns at or past ncols[b] are not written.  Each stream's sums are those of scatter32.
@@ -449,7 +454,8 @@ void drop_graphs(mm_plan_t pl);
 int build_batch_layout(mm_plan_t pl);
 PcgCtl batch_ctl(mm_plan_t pl);
 // part slot `slot` of every masked problem <- partials of a^T b
-int vec_dot(mm_plan_t pl, const double* a, const double* b, int slot, const PcgCtl& ctl);
+int vec_dot(mm_plan_t pl, const double* a, const double* b, int slot, const PcgCtl& ctl,
+            const int64_t* wave_off = nullptr);
 int pcg_update_xr(mm_plan_t pl, double* x, double* r, const double* p, const double* q,
                   const PcgCtl& ctl);
 // the x, r update followed by z = M_BD r, with partials of ||r||^2 and r^T z

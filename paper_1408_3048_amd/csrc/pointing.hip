@@ -204,13 +204,20 @@ __device__ __forceinline__ int wave_of_block() {
 // scan goes lane to lane by DPP instead of through LDS: FP64 at 2^14 / 2^20 / 2^22 samples
 // 5.75 / 11.6 / 35.0 -> 4.9 / 10.9 / 31.5 us, FP32 at 2^20 / 2^24 7.8 / 58.2 -> 6.5 / 56.0 us,
 // ring scan of 2^25 174 -> 170, 8 columns at 2^24 254 -> 240, block sums of M_BD with them.
-template <typename T, int NS, int E>
+//
+// DOT: the wave also adds up dot^T x over its pixels, for the p^T A p of a PCG iteration, where
+// the problem's ranges are few enough for one partial each (kVecBlocks, 2^18 samples): a launch
+// less in iterations that are bound by their launches.  38 iterations at 2^18 samples of one
+// Stokes parameter 1540 -> 1405 us, 27 at 2^14 (IQU) 1054 -> 995.
+template <typename T, int NS, int E, bool DOT>
 __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scatter(const int32_t* __restrict__ perm,
                                                  const T* __restrict__ ws, const T* __restrict__ z,
                                                  const unsigned long long* __restrict__ heads,
                                                  const WaveRange* __restrict__ rng,
                                                  int64_t n_waves, double* __restrict__ out,
-                                                 const int* __restrict__ mask) {
+                                                 const int* __restrict__ mask,
+                                                 const double* __restrict__ dot,
+                                                 double* __restrict__ part) {
     static_assert(E % 4 == 0, "E must be a multiple of 4");
     __shared__ __align__(16) T zx[4][64 * E];
     // the blocks of one XCD take a contiguous range of waves (neighbouring pixels share the
@@ -311,11 +318,22 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
             for (int e = 0; e < E; ++e) v[e][0] = zz[e];
         }
     };
+    double acc = 0.0;
     auto emit = [&](int32_t pix, const T* tot) {
 #pragma unroll
         for (int q = 0; q < NS; ++q) out[(int64_t)pix * NS + q] = (double)tot[q];
+        if constexpr (DOT) {
+#pragma unroll
+            for (int q = 0; q < NS; ++q) acc += dot[(int64_t)pix * NS + q] * (double)tot[q];
+        }
     };
     seg_reduce<T, NS, E>(i0, i1, wr.p0, heads, load, emit);
+    if constexpr (DOT) {
+        if (wr.slot < 0) return;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) acc += __shfl_down(acc, d);
+        if (lane == 0) part[(int64_t)wr.prob * kVecBlocks + wr.slot] = acc;
+    }
 }
 
 // P^T of NC FP32 time streams z + k zstride (k < NC), the A Z columns of the coarse space
@@ -599,22 +617,28 @@ inline int grid_for(int64_t n, int threads = 256, int cap = 65536) {
     return (int)g;
 }
 
-template <typename T>
-int scatter_t(mm_plan_t pl, const T* z, const T* ws, double* x, const int* mask) {
+template <typename T, int NS, bool DOT>
+int launch_scatter(mm_plan_t pl, const T* z, const T* ws, double* x, const int* mask,
+                   const double* dot) {
     const int64_t nb = (pl->n_waves + 3) / 4;
     if (nb == 0) return MM_OK;
     // 4 samples per lane: 8 gathers more per lane cost the residency they would add
-    constexpr int E = 4;
-    if (pl->n_s == 3)
-        hipLaunchKernelGGL((k_scatter<T, 3, E>), dim3(xcd_grid(nb)), dim3(256), 0, pl->stream, pl->perm.p, ws,
-                           z, (const unsigned long long*)pl->heads.p, pl->wave_rng.p, pl->n_waves,
-                           x, mask);
-    else
-        hipLaunchKernelGGL((k_scatter<T, 1, E>), dim3(xcd_grid(nb)), dim3(256), 0, pl->stream, pl->perm.p, ws,
-                           z, (const unsigned long long*)pl->heads.p, pl->wave_rng.p, pl->n_waves,
-                           x, mask);
+    hipLaunchKernelGGL((k_scatter<T, NS, 4, DOT>), dim3(xcd_grid(nb)), dim3(256), 0, pl->stream,
+                       pl->perm.p, ws, z, (const unsigned long long*)pl->heads.p, pl->wave_rng.p,
+                       pl->n_waves, x, mask, dot,
+                       pl->part.p + (int64_t)kSlotPQ * pl->n_prob * kVecBlocks);
     MM_HIP(hipGetLastError());
     return MM_OK;
+}
+
+template <typename T>
+int scatter_t(mm_plan_t pl, const T* z, const T* ws, double* x, const int* mask,
+              const double* dot) {
+    if (dot && pl->n_slotted > 0)
+        return pl->n_s == 3 ? launch_scatter<T, 3, true>(pl, z, ws, x, mask, dot)
+                            : launch_scatter<T, 1, true>(pl, z, ws, x, mask, dot);
+    return pl->n_s == 3 ? launch_scatter<T, 3, false>(pl, z, ws, x, mask, nullptr)
+                        : launch_scatter<T, 1, false>(pl, z, ws, x, mask, nullptr);
 }
 
 }  // namespace
@@ -644,12 +668,12 @@ int scatter_cols32(mm_plan_t pl, const float* z, int64_t zstride, int nc, int k0
     return MM_OK;
 }
 
-int scatter64(mm_plan_t pl, const double* z, double* x, const int* mask) {
-    return scatter_t<double>(pl, z, pl->ws64.p, x, mask);
+int scatter64(mm_plan_t pl, const double* z, double* x, const int* mask, const double* dot) {
+    return scatter_t<double>(pl, z, pl->ws64.p, x, mask, dot);
 }
 
-int scatter32(mm_plan_t pl, const float* z, double* x, const int* mask) {
-    return scatter_t<float>(pl, z, pl->ws32.p, x, mask);
+int scatter32(mm_plan_t pl, const float* z, double* x, const int* mask, const double* dot) {
+    return scatter_t<float>(pl, z, pl->ws32.p, x, mask, dot);
 }
 
 int depoint(mm_plan_t pl, const double* x, void* y, int y_f64) {

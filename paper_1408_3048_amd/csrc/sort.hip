@@ -294,7 +294,7 @@ __global__ void k_wave_ranges(const int64_t* __restrict__ seg, const int32_t* __
         r.p0 = (int32_t)p0;
         r.p1 = (int32_t)p1;
         r.prob = b;
-        r.pad = 0;
+        r.slot = woff[b + 1] - woff[b] <= kVecBlocks ? (int32_t)k : -1;
         rng[w] = r;
     }
 }
@@ -621,6 +621,8 @@ int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves) {
         woff[b + 1] = woff[b] + (pl->h_pn[b] + pw[b] - 1) / pw[b];
     }
     pl->n_waves = woff[B];
+    pl->n_slotted = 0;
+    for (int b = 0; b < B; ++b) pl->n_slotted += woff[b + 1] - woff[b] <= kVecBlocks;
     pl->pt_range = per_wave;
     DBuf<int64_t> d_pw;
     MM_TRY(d_pw.alloc(B));

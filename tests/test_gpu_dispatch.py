@@ -355,3 +355,30 @@ def test_dense_coarse_columns_in_groups(max_cols, ns):
         bar = 2.0 ** -23 * np.linalg.norm(z, axis=1)[:, None] * np.linalg.norm(az, axis=1)[None]
         assert (np.abs(e - ref) <= np.maximum(bar, bar.T)).all()
     p.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_dot_products_by_pt_ranges_in_a_batch_of_small_and_large_problems(precision):
+    """p^T A p comes from P^T's ranges where a problem has at most 512 (2^18 samples) and from a
+    launch of its own where it has more: a batch of 2^14, 2^18 (512 ranges), and just over 2^18
+    samples equals the standalone plans bit for bit over the iterations it is given, and the
+    recorded residuals are those of the solution."""
+    kw = dict(n_det=4, lam=64, fknee_range=(0.5, 1.0), alpha_range=(1.0, 1.5))
+    scans = [synth.raster_iqu(side=s, spp=8, interval_len=s * s * 4, seed_key=70 + s, **kw)
+             for s in (16, 64, 65)]
+    assert [len(sc.noise) for sc in scans] == [1 << 14, 1 << 18, 270400]
+    opts = dict(precision="mixed", fft_len_f64=4096, fft_len_f32=4096)
+    pb = _gpu_plan(scans, **opts)
+    off = pb.problem_pixels() * 3
+    d = torch.from_numpy(np.concatenate([sc.noise for sc in scans])).cuda()
+    xb, ib = pb.pcg_solve(pb.rhs(d), precision=precision, tol=1e-8, max_iter=3000)
+    for b, sc in enumerate(scans):
+        p1 = Plan.from_scan(sc, **opts)
+        rhs = p1.rhs(torch.from_numpy(sc.noise).cuda())
+        x1, i1 = p1.pcg_solve(rhs, precision=precision, tol=1e-8, max_iter=3000)
+        assert torch.equal(x1, xb[off[b]:off[b + 1]]), b
+        assert np.array_equal(i1["history"], ib["problems"][b]["history"])
+        res = float((rhs - p1.apply_A(x1)).norm() / rhs.norm())
+        assert res <= 1.01e-8
+        p1.close()
+    pb.close()
