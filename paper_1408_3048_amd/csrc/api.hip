@@ -335,6 +335,15 @@ constexpr double kReplaceRatio = 1e-4;
 constexpr int kChunk = 4;
 // samples from which launches issued one by one are as fast as replayed ones
 constexpr int64_t kGraphMaxSamples = int64_t(1) << 18;
+// Whether a plan's solves with preconditioner pc replay graphs.  The two-level iterations (8
+// launches and more) of small plans do: 21 iterations at 2^16 samples 1058 us against 1068,
+// with A-DEF2 1273 against 1304.  The 4 launches of a block-Jacobi iteration do not (2^14
+// samples 1049 against 995, 2^16 1060 against 1056), and from 2^18 samples on launches issued one
+// by one are as fast or faster (2^22 FP64 two-level 6470 replayed against 6350, 2^24 mixed
+// two-level 15820 against 15690, 48 problems of 150000 samples 6990 against 6790).
+bool graph_pays(mm_plan_t pl, int pc) {
+    return pl->opts.graph != 0 && pl->n_t < kGraphMaxSamples && pc != MM_BJ;
+}
 
 double ms_since(clk::time_point t0) {
     return std::chrono::duration<double, std::milli>(clk::now() - t0).count();
@@ -480,14 +489,10 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
     };
     // graph of one chunk of kChunk iterations for this operator / preconditioner and control
     // arguments (one launch per chunk: the gaps between graph launches are paid once).
-    // Capture and instantiation take 110-370 us and the replays of small problems save 24 us a
-    // solve (27 iterations, 2^14 samples: 1097 us against 1121), so they come with the second
-    // solve that a plan does with the same arguments.  From kGraphMaxSamples on launches issued
-    // one by one are as fast or faster: 2^18 samples 1590 us both ways, 2^22 FP64 two-level
-    // 6470 replayed against 6350, 2^24 mixed two-level 15820 against 15690, 48 problems of
-    // 150000 samples 6990 against 6790.
-    const bool use_graph = pl->opts.graph != 0 && !pl->prof_on && pl->gstream != nullptr &&
-                           pl->stream == pl->gstream && pl->n_t < kGraphMaxSamples;
+    // Capture and instantiation take 110-370 us, so they come with the second solve that a plan
+    // does with the same arguments.
+    const bool use_graph = pl->gstream != nullptr && pl->stream == pl->gstream && !pl->prof_on &&
+                           graph_pays(pl, ea.pc);
     const int gi = ea.op32 ? 1 : 0, gj = ea.pc;
     hipGraphExec_t& gx = pl->gexec[gi][gj];
     auto& key = pl->gkey[gi][gj];
@@ -1055,14 +1060,14 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
     }
     const auto t0 = clk::now();
     const int B = pl->n_prob;
-    // the solve runs on the plan's own non-blocking stream (graph capture needs one),
-    // ordered after the caller's stream and synchronised before returning
+    // a solve that replays graphs runs on the plan's own non-blocking stream (capture needs
+    // one), ordered after the caller's stream and synchronised before returning
     hipStream_t user = pl->stream;
     AllocStream alloc_scope(user);  // plan buffers always live on the caller's stream
     MM_TRY(ensure_solver_buffers(pl, max_iter));
-    if (pl->opts.graph && !pl->gstream)
-        MM_HIP(hipStreamCreateWithFlags(&pl->gstream, hipStreamNonBlocking));
-    if (pl->opts.graph) {
+    if (graph_pays(pl, pc)) {
+        if (!pl->gstream)
+            MM_HIP(hipStreamCreateWithFlags(&pl->gstream, hipStreamNonBlocking));
         MM_HIP(hipStreamSynchronize(user));
         pl->stream = pl->gstream;
     }
