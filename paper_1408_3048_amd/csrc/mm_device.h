@@ -12,6 +12,33 @@
 
 namespace mm {
 
+// A lane's value from another lane by data-parallel primitives: row_shr:n (lane - n of the
+// same row of 16), row_bcast:15 / :31 (last lane of the row / of the two rows before the
+// lane's), wave_shr:1 (lane - 1); 0 where there is no such lane.
+// ROWS: the rows of 16 lanes that take part (the others get 0).
+constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143, kWaveShr1 = 0x138;
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true),
+        __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true));
+}
+
+// sum of v over the wave, in its last lane
+__device__ __forceinline__ float wave_sum_last(float v) {
+    v += dpp<kRowShr + 1>(v);
+    v += dpp<kRowShr + 2>(v);
+    v += dpp<kRowShr + 4>(v);
+    v += dpp<kRowShr + 8>(v);
+    v += dpp<kRowBcast15, 0xa>(v);
+    v += dpp<kRowBcast31, 0xc>(v);
+    return v;
+}
+
 // block sum of v (one value per thread; blockDim.x a multiple of 64, at most 1024): wave
 // shuffle trees, then the per-wave sums in wave order; the same in every block, returned to
 // all threads.  All threads must call.

@@ -11,20 +11,6 @@
 namespace mm {
 namespace {
 
-// A lane's value from another lane by data-parallel primitives: row_shr:n (lane - n of the
-// same row of 16), row_bcast:15 / :31 (last lane of the row / of the two rows before the
-// lane's), wave_shr:1 (lane - 1); 0 where there is no such lane.
-constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143, kWaveShr1 = 0x138;
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-    return __hiloint2double(
-        __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true),
-        __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true));
-}
 __device__ __forceinline__ float last_lane(float x) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
