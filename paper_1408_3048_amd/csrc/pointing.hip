@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "mm_device.h"
+#include "mm_pos.h"
 
 namespace mm {
 namespace {
@@ -33,8 +34,8 @@ __device__ __forceinline__ void scan_step(T (&acc)[NV], bool take) {
 // Wave-level segmented reduction over pixel-sorted samples.
 //
 // A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., counted from a
-// multiple of 64 at or below the first (32-bit positions: the caller moves its pointers
-// there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
+// multiple of 64 at or below the first (32-bit positions, see mm_pos.h: the caller moves its
+// pointers there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
 // (e < E), loaded with aligned vector loads so E gathers are in flight per lane.
 // Each lane first sums its own samples segment by segment, then one segmented
 // inclusive scan over the 64 lane summaries (flag: the lane holds a segment
@@ -44,7 +45,7 @@ __device__ __forceinline__ void scan_step(T (&acc)[NV], bool take) {
 // the plan, so results are deterministic; samples outside [i0, i1) are zeros.
 // `load(base, valid, v)` fills v[e][.] for the E samples; `emit(pixel, val)`.
 template <typename T, int NV, int E, class Load, class Emit>
-__device__ __forceinline__ void seg_reduce(int i0, int i1, int32_t p0,
+__device__ __forceinline__ void seg_reduce(pos_t i0, pos_t i1, int32_t p0,
                                            const unsigned long long* __restrict__ heads,
                                            Load&& load, Emit&& emit) {
     static_assert(64 % E == 0, "E must divide 64");
@@ -53,15 +54,15 @@ __device__ __forceinline__ void seg_reduce(int i0, int i1, int32_t p0,
 #pragma unroll
     for (int q = 0; q < NV; ++q) carry[q] = (T)0;
     int32_t pprev = p0 - 1;
-    for (int c = i0 & ~(E - 1); c < i1; c += 64 * E) {
-        const int base = c + E * lane;
+    for (pos_t c = first_chunk(i0, E); c < i1; c = next_chunk(c, E)) {
+        const pos_t base = lane_base(c, lane, E);
         bool valid[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) valid[e] = base + e >= i0 && base + e < i1;
         // segment-start words of the lane's samples and of the sample after them, loaded
         // unconditionally (a valid word for lanes past the range) ahead of the samples, so
         // that a chunk's loads are in flight together; their bits are read after load()
-        const int inext = base + E;
+        const pos_t inext = base + E;
         const unsigned long long hw = heads[(base < i1 ? base : i0) >> 6];
         const unsigned long long hn = heads[(inext < i1 ? inext : i0) >> 6];
         T v[E][NV];
@@ -128,7 +129,7 @@ __device__ __forceinline__ void seg_reduce(int i0, int i1, int32_t p0,
             T tot[NV];
 #pragma unroll
             for (int q = 0; q < NV; ++q) tot[q] = seen[e] ? sl[e][q] : sl[e][q] + pre[q];
-            const int i = base + e;
+            const pos_t i = base + e;
             bool end = false;
             if (valid[e]) {
                 if (i + 1 == i1) end = true;
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
     if (mask && !mask[wr.prob]) return;
     // positions from a multiple of 64
     const int64_t c0 = wr.i0 & ~(int64_t)63;
-    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;
     heads += c0 >> 6;
@@ -229,17 +230,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
     // guarded loads become one branch each, and the compiler then waits for every load
     // before issuing the next.
     int32_t pf[E];
-    auto fetch = [&](int c) {
+    auto fetch = [&](pos_t c) {
 #pragma unroll
         for (int g = 0; g < E; ++g) {
-            const int i = c + lane + 64 * g;
+            const pos_t i = c + lane + 64 * g;
             const bool in = i >= i0 && i < i1;
             const int32_t t = ld_stream(perm + (in ? i : i0));
             pf[g] = in ? t : -1;
         }
     };
-    fetch(i0 & ~(E - 1));
-    auto load = [&](int base, const bool* valid, T (*v)[NS]) {
+    fetch(first_chunk(i0, E));
+    auto load = [&](pos_t base, const bool* valid, T (*v)[NS]) {
         // the sorted weights are loaded first, so their latency overlaps the z gather's
         // (loads after the exchange below would wait for it); lanes past the range skip them
         T wv[2 * E];
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
                 if constexpr (sizeof(T) == 4) {
 #pragma unroll
                     for (int g = 0; g < E / 2; ++g) {
-                        const float4 a = ld_stream4(ws + 2 * base + 4 * g);
+                        const float4 a = ld_stream4(ws + weight_index(base) + 4 * g);
                         wv[4 * g] = a.x;
                         wv[4 * g + 1] = a.y;
                         wv[4 * g + 2] = a.z;
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
                 } else {
 #pragma unroll
                     for (int e = 0; e < E; ++e) {
-                        const double2 a = ld_stream2(ws + 2 * (base + e));
+                        const double2 a = ld_stream2(ws + weight_index(base + e));
                         wv[2 * e] = a.x;
                         wv[2 * e + 1] = a.y;
                     }
@@ -268,11 +269,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
             }
         }
         // every lane takes part in the exchange, also lanes past the range
-        const int c = base - E * lane;
+        const pos_t c = base - E * lane;
         int32_t tc[E];
 #pragma unroll
         for (int g = 0; g < E; ++g) tc[g] = pf[g];
-        fetch(c + 64 * E);
+        fetch(next_chunk(c, E));
         T zg[E];
 #pragma unroll
         for (int g = 0; g < E; ++g) zg[g] = z[tc[g] >= 0 ? tc[g] : 0];
@@ -351,30 +352,30 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
     float* const azb = az + blk_off[b] + (int64_t)k0 * n_vec - q0 * NS;  // pixel q0 at 0
     // positions from a multiple of 64
     const int64_t c0 = wr.i0 & ~(int64_t)63;
-    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;
     heads += c0 >> 6;
     const int lane = threadIdx.x & 63;
     float (*zw)[64 * E] = zx[threadIdx.x >> 6];
     int32_t pf[E];
-    auto fetch = [&](int c) {
+    auto fetch = [&](pos_t c) {
 #pragma unroll
         for (int g = 0; g < E; ++g) {
-            const int i = c + lane + 64 * g;
+            const pos_t i = c + lane + 64 * g;
             const bool in = i >= i0 && i < i1;
             const int32_t t = ld_stream(perm + (in ? i : i0));
             pf[g] = in ? t : -1;
         }
     };
-    fetch(i0 & ~(E - 1));
-    auto load = [&](int base, const bool* valid, float (*v)[NV]) {
+    fetch(first_chunk(i0, E));
+    auto load = [&](pos_t base, const bool* valid, float (*v)[NV]) {
         float wv[2 * E];
         if constexpr (NS == 3) {
             if (base < i1) {
 #pragma unroll
                 for (int g = 0; g < E / 2; ++g) {
-                    const float4 a = ld_stream4(ws + 2 * base + 4 * g);
+                    const float4 a = ld_stream4(ws + weight_index(base) + 4 * g);
                     wv[4 * g] = a.x;
                     wv[4 * g + 1] = a.y;
                     wv[4 * g + 2] = a.z;
@@ -385,11 +386,11 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
                 for (int e = 0; e < 2 * E; ++e) wv[e] = 0.0f;
             }
         }
-        const int c = base - E * lane;
+        const pos_t c = base - E * lane;
         int32_t tc[E];
 #pragma unroll
         for (int g = 0; g < E; ++g) tc[g] = pf[g];
-        fetch(c + 64 * E);
+        fetch(next_chunk(c, E));
         // streams past nc load stream 0 (unconditional loads; never written out)
         float zg[NC][E];
 #pragma unroll
@@ -488,11 +489,11 @@ __global__ __launch_bounds__(256) void k_bj_build(
     int64_t jlo = 0, jhi = 0;
     double dj = 0.0;
     const int64_t c0 = wr.i0 & ~(int64_t)63;  // positions from a multiple of 64
-    const int i0 = (int)(wr.i0 - c0), i1 = (int)(wr.i1 - c0);
+    const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;
     heads += c0 >> 6;
-    auto load = [&](int base, const bool* valid, double (*v)[NV]) {
+    auto load = [&](pos_t base, const bool* valid, double (*v)[NV]) {
         int64_t tt[E];
         double wa[E], wb[E];
 #pragma unroll
