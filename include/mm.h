@@ -93,11 +93,11 @@ typedef struct {
                           operator; 0 = automatic */
     int fft_len_f32;   /* same for the FP32 operator; 0 = automatic */
     void* stream;      /* hipStream_t; NULL = default stream */
-    int graph;         /* 1 (default): solves with a two-level preconditioner on plans of less
-                          than 2^18 samples run on a plan-owned non-blocking stream, capture
-                          their iterations in a HIP graph at the second solve with the same
-                          arguments and replay it; 0, and other solves: plain launches on the
-                          caller's stream */
+    int graph;         /* 1 (default): a solve runs on a non-blocking stream of its own, after the
+                          work on the caller's stream (solves of several threads overlap); with
+                          a two-level preconditioner on plans of less than 2^18 samples its
+                          iterations are captured in a HIP graph at the second solve with the
+                          same arguments and replayed; 0: plain launches on the caller's stream */
     int autotune;      /* 1: mm_plan times the candidate FFT lengths on the plan's own data
                           and keeps the fastest (when fft_len_* is 0); 0 (default): cost model */
     int az_fp16;       /* mixed plans with Z_S: 1 (default) the two-level (A-DEF1) apply reads

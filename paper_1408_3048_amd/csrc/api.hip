@@ -231,6 +231,39 @@ void pinned_free(void* p, size_t bytes) {
     (void)hipHostFree(p);
 }
 
+// Non-blocking streams for solves, kept per device between them: the runtime takes 46-110 us to
+// make one.  A solve has one to itself and gives it back when its work there is done; at most
+// kStreamCap idle ones are kept.
+constexpr size_t kStreamCap = 8;
+std::map<int, std::vector<hipStream_t>> g_streams;  // idle streams per device (g_cache_mu)
+
+int stream_take(int* dev, hipStream_t* st) {
+    MM_HIP(hipGetDevice(dev));
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        auto& idle = g_streams[*dev];
+        if (!idle.empty()) {
+            *st = idle.back();
+            idle.pop_back();
+            return MM_OK;
+        }
+    }
+    MM_HIP(hipStreamCreateWithFlags(st, hipStreamNonBlocking));
+    return MM_OK;
+}
+
+void stream_give(int dev, hipStream_t st) {
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        auto& idle = g_streams[dev];
+        if (idle.size() < kStreamCap) {
+            idle.push_back(st);
+            return;
+        }
+    }
+    (void)hipStreamDestroy(st);
+}
+
 // RAII: the stream for allocations made during one API call
 struct AllocStream {
     hipStream_t prev;
@@ -335,7 +368,7 @@ constexpr double kReplaceRatio = 1e-4;
 constexpr int kChunk = 4;
 // samples from which launches issued one by one are as fast as replayed ones
 constexpr int64_t kGraphMaxSamples = int64_t(1) << 18;
-// Whether a plan's solves with preconditioner pc replay graphs.  The two-level iterations (8
+// Whether a plan's solves with preconditioner pc, on a stream of their own, replay graphs.  The two-level iterations (8
 // launches and more) of small plans do: 21 iterations at 2^16 samples 1058 us against 1068,
 // with A-DEF2 1273 against 1304.  The 4 launches of a block-Jacobi iteration do not (2^14
 // samples 1049 against 995, 2^16 1060 against 1056), and from 2^18 samples on launches issued one
@@ -491,8 +524,7 @@ int pcg_engine(mm_plan_t pl, const double* b, double* x, const EngineArgs& ea) {
     // arguments (one launch per chunk: the gaps between graph launches are paid once).
     // Capture and instantiation take 110-370 us, so they come with the second solve that a plan
     // does with the same arguments.
-    const bool use_graph = pl->gstream != nullptr && pl->stream == pl->gstream && !pl->prof_on &&
-                           graph_pays(pl, ea.pc);
+    const bool use_graph = pl->own_stream && !pl->prof_on && graph_pays(pl, ea.pc);
     const int gi = ea.op32 ? 1 : 0, gj = ea.pc;
     hipGraphExec_t& gx = pl->gexec[gi][gj];
     auto& key = pl->gkey[gi][gj];
@@ -588,10 +620,6 @@ mm_plan_s::~mm_plan_s() {
     for (auto& row : gexec)
         for (auto& g : row)
             if (g) (void)hipGraphExecDestroy(g);
-    if (gstream) {
-        (void)hipStreamSynchronize(gstream);
-        (void)hipStreamDestroy(gstream);
-    }
     pinned_free(h_sc, sizeof(PcgScalars) * n_prob);
     for (auto& v : prof_ev)
         for (auto& r : v) {
@@ -1060,25 +1088,31 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
     }
     const auto t0 = clk::now();
     const int B = pl->n_prob;
-    // a solve that replays graphs runs on the plan's own non-blocking stream (capture needs
-    // one), ordered after the caller's stream and synchronised before returning
+    // a solve runs on a non-blocking stream of its own, ordered after the caller's stream and
+    // synchronised before returning: solves of other threads on the same stream overlap with it,
+    // what is enqueued there meanwhile does not hold up its reads of the problem states, and its
+    // iterations can be captured (on the caller's stream with graph = 0)
     hipStream_t user = pl->stream;
     AllocStream alloc_scope(user);  // plan buffers always live on the caller's stream
     MM_TRY(ensure_solver_buffers(pl, max_iter));
-    if (graph_pays(pl, pc)) {
-        if (!pl->gstream)
-            MM_HIP(hipStreamCreateWithFlags(&pl->gstream, hipStreamNonBlocking));
-        MM_HIP(hipStreamSynchronize(user));
-        pl->stream = pl->gstream;
-    }
     struct Restore {
         mm_plan_t pl;
         hipStream_t user;
+        int dev;
         ~Restore() {
             (void)hipStreamSynchronize(pl->stream);
+            if (pl->own_stream) stream_give(dev, pl->stream);
+            pl->own_stream = false;
             pl->stream = user;
         }
-    } restore{pl, user};
+    } restore{pl, user, 0};
+    if (pl->opts.graph) {
+        MM_HIP(hipStreamSynchronize(user));
+        hipStream_t own;
+        MM_TRY(stream_take(&restore.dev, &own));
+        pl->stream = own;
+        pl->own_stream = true;
+    }
     std::vector<mm_solve_info> loc(B);
     mm_solve_info* inf = info ? info : loc.data();
     for (int i = 0; i < B; ++i) {
@@ -1097,8 +1131,12 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
             if (wanted(i)) len = std::max<size_t>(len, std::max(pl->h_sc[i].iter, 0));
         if (len == 0) return MM_OK;
         std::vector<double> h(len * B);
-        MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, pl->hist.p, (size_t)pl->hstride * 8, len * 8, B,
-                                hipMemcpyDeviceToHost, pl->stream));
+        // (a 2-D copy waits for the default stream as well)
+        if (B == 1)
+            MM_HIP(hipMemcpyAsync(h.data(), pl->hist.p, len * 8, hipMemcpyDeviceToHost, pl->stream));
+        else
+            MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, pl->hist.p, (size_t)pl->hstride * 8, len * 8,
+                                    B, hipMemcpyDeviceToHost, pl->stream));
         MM_HIP(hipStreamSynchronize(pl->stream));
         for (int i = 0; i < B; ++i)
             for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)

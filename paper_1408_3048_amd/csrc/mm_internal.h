@@ -315,7 +315,7 @@ struct mm_plan_s {
     } krec;
     // captured PCG iteration (one per operator precision / preconditioner MM_BJ, MM_2LVL,
     // MM_ADEF2)
-    hipStream_t gstream = nullptr;      // non-blocking stream the graphs are captured on
+    bool own_stream = false;            // `stream` is a solve's own (graphs are captured there)
     hipGraphExec_t gexec[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
     struct GraphKey {          // control arguments of the last solve, baked into its graph
         int replace = -1;
