@@ -319,7 +319,8 @@ int mm_pt_range(mm_plan_t plan);
  * [N_t]): c_j(0) = sum_t u_t v_t and c_j(k) = sum_t (u_t v_{t+k} + u_{t+k} v_t) for
  * k = 1..K_j = min(lambda, t_j - 1), t and t+k in interval j, so that u_j^T T_j v_j =
  * sum_k t_k c_j(k) for the band Toeplitz block T_j [Sect. 2.1, eq. N_def].  dev_out:
- * device FP64 [n_intervals][lambda+1], zero past K_j.  Deterministic.  Synchronises. */
+ * device FP64 [n_intervals][lambda+1], zero past K_j.  Each lag's rounding follows the sum of its
+ * own terms' magnitudes.  Deterministic.  Synchronises. */
 int mm_lag_correlations(mm_plan_t plan, const double* u, const double* v, double* dev_out);
 
 /* Derivatives of the windowed Toeplitz taps of every interval with respect to its noise
