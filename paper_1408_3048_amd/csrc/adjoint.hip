@@ -161,7 +161,7 @@ __global__ void k_lag0_sum(const double* __restrict__ part, const int64_t* __res
 // (bursts, flagged stretches, lags near the interval's length).  The same launches correlate |u|
 // and |v|, which gives S_j(k), and blocks of kLcLags lags that hold one with S_j(k) < P_j / 8, or
 // one that is not finite, are taken by direct sums: every lag keeps a rounding of its own terms.
-// (Gaussian u and v have S_j(k) = 0.6 (1 - k / t_j) P_j.)
+// (Gaussian u and v have S_j(k) of about (1 - k / t_j) P_j.)
 //
 // The transform's length goes by K_j = min(lambda, t_j - 1), so that intervals shorter than the
 // band take what they need; lag 0 alone (lambda = 0) and lags past 4096 are direct sums.

@@ -20,6 +20,7 @@
 // transformed in place by decimation in time (bit-reversed in, natural out),
 // so no explicit permutation pass is needed.  Both transforms run as radix-16
 // passes held in registers with one LDS exchange per pass.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -1028,11 +1029,15 @@ __global__ void k_taps_sum(const int32_t* __restrict__ kid, const int32_t* __res
 // intervals of distinct length, direct / chirps: about 40009 samples and 2049 lags 4.99 / 1.86
 // ms, 8195 samples 1.72 / 1.08; error of the taps against extended precision, relative to
 // their norm, 0.7-6.8e-15 / 0.2-6.4e-16.
+// A launch holds the chirps (128 KB a length) and the partial rows of at most kCztScratch; more
+// kernels go in turn.  A workgroup adds up several segments where an interval has more than
+// kCztMaxRows.
 struct CztSeg {
-    int32_t g;      // kernel
-    int32_t chirp;  // its length's chirp
-    int64_t m0;     // first frequency
+    int32_t g;       // kernel
+    int32_t chirp;   // its length's chirp
+    int64_t m0, m1;  // frequencies
 };
+constexpr int64_t kCztScratch = (int64_t)128 << 20, kCztMaxRows = 1024;
 
 template <int LOGM, int NT>
 __global__ __launch_bounds__(NT) void k_czt_chirp(const int32_t* __restrict__ len, int lam,
@@ -1073,36 +1078,40 @@ __global__ __launch_bounds__(NT) void k_taps_czt(const CztSeg* __restrict__ seg,
     const int64_t n = klen[sg.g];
     const int K = (int)(n - 1 < lam ? n - 1 : lam);
     const double sigma = kpar[3 * sg.g], fk = kpar[3 * sg.g + 1], al = kpar[3 * sg.g + 2];
-    for (int i = threadIdx.x; i < M; i += NT) {
-        const int64_t m = sg.m0 + i;
-        double re = 0.0, im = 0.0;
-        if (i < M - K && 2 * m <= n) {
-            const double a = (m == 0 || 2 * m == n ? 1.0 : 2.0) *
-                             inv_psd_at(m, n, f_samp, sigma, fk, al, what);
-            double sn, cs;
-            sincospi((double)((int64_t)i * i % (2 * n)) / (double)n, &sn, &cs);
-            re = a * cs;
-            im = -a * sn;
-        }
-        buf.put(i, re, im);
-    }
-    __syncthreads();
-    fwd_passes<double, LOGM, NT, LOGM>(buf, tw);
     const double2* ch = chirp + (int64_t)sg.chirp * M;
-    for (int i = threadIdx.x; i < M; i += NT) {
-        const double2 z = ch[i];
-        double re, im;
-        buf.get(i, re, im);
-        buf.put(i, re * z.x - im * z.y, re * z.y + im * z.x);
-    }
-    __syncthreads();
-    inv_passes<double, LOGM, NT, LOGM>(buf, tw);
     double* out = part + (int64_t)blockIdx.x * kstride;
-    for (int k = threadIdx.x; k <= K; k += NT) {
-        double sn, cs, re, im;
-        sincospi((double)((int64_t)k * (k + 2 * sg.m0) % (2 * n)) / (double)n, &sn, &cs);
-        buf.get(k, re, im);
-        out[k] = (cs * re + sn * im) * (1.0 / M);
+    for (int64_t m0 = sg.m0; m0 < sg.m1; m0 += M - K) {
+        for (int i = threadIdx.x; i < M; i += NT) {
+            const int64_t m = m0 + i;
+            double re = 0.0, im = 0.0;
+            if (i < M - K && 2 * m <= n) {
+                const double a = (m == 0 || 2 * m == n ? 1.0 : 2.0) *
+                                 inv_psd_at(m, n, f_samp, sigma, fk, al, what);
+                double sn, cs;
+                sincospi((double)((int64_t)i * i % (2 * n)) / (double)n, &sn, &cs);
+                re = a * cs;
+                im = -a * sn;
+            }
+            buf.put(i, re, im);
+        }
+        __syncthreads();
+        fwd_passes<double, LOGM, NT, LOGM>(buf, tw);
+        for (int i = threadIdx.x; i < M; i += NT) {
+            const double2 z = ch[i];
+            double re, im;
+            buf.get(i, re, im);
+            buf.put(i, re * z.x - im * z.y, re * z.y + im * z.x);
+        }
+        __syncthreads();
+        inv_passes<double, LOGM, NT, LOGM>(buf, tw);
+        for (int k = threadIdx.x; k <= K; k += NT) {
+            double sn, cs, re, im;
+            sincospi((double)((int64_t)k * (k + 2 * m0) % (2 * n)) / (double)n, &sn, &cs);
+            buf.get(k, re, im);
+            const double r = (cs * re + sn * im) * (1.0 / M);
+            out[k] = m0 == sg.m0 ? r : out[k] + r;
+        }
+        __syncthreads();  // the next segment overwrites the buffer
     }
 }
 
@@ -1375,23 +1384,32 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
                            pl->opts.window, d_t.p);
         MM_HIP(hipGetLastError());
     }
-    if (!czt_ids.empty()) {
-        const int nf = (int)czt_ids.size();
+    // kernels of one length are neighbours and share its chirp
+    std::sort(czt_ids.begin(), czt_ids.end(), [&](int32_t a, int32_t b) {
+        return pl->h_kern_len[a] != pl->h_kern_len[b] ? pl->h_kern_len[a] < pl->h_kern_len[b]
+                                                      : a < b;
+    });
+    for (size_t i0 = 0, i1; i0 < czt_ids.size(); i0 = i1) {
         int kmax = 1;
+        for (size_t i = i0; i < czt_ids.size(); ++i)
+            kmax = std::max<int>(kmax, (int)tcnt[czt_ids[i]]);
+        std::vector<int32_t> ids, lens;
         std::vector<int64_t> poff(1, 0);
         std::vector<CztSeg> seg;
-        std::map<int32_t, int32_t> of_len;  // interval length -> chirp
-        std::vector<int32_t> lens;
-        for (int g : czt_ids) {
-            const int32_t n = pl->h_kern_len[g];
-            const auto it = of_len.emplace(n, (int32_t)lens.size());
-            if (it.second) lens.push_back(n);
-            const int64_t step = kCz - (tcnt[g] - 1);
-            for (int64_t m0 = 0; m0 <= n / 2; m0 += step) seg.push_back({g, it.first->second, m0});
+        for (i1 = i0; i1 < czt_ids.size(); ++i1) {
+            const int32_t g = czt_ids[i1], n = pl->h_kern_len[g];
+            const int64_t step = kCz - (tcnt[g] - 1), ns = n / 2 / step + 1;
+            const int64_t run = (ns + kCztMaxRows - 1) / kCztMaxRows * step;
+            const int64_t rows = (n / 2 + run) / run, nl = (int64_t)lens.size() + 1;
+            if (i1 > i0 && nl * kCz * 16 + ((int64_t)seg.size() + rows) * kmax * 8 > kCztScratch)
+                break;
+            if (lens.empty() || lens.back() != n) lens.push_back(n);
+            for (int64_t m0 = 0; m0 <= n / 2; m0 += run)
+                seg.push_back({g, (int32_t)lens.size() - 1, m0, std::min<int64_t>(m0 + run, n / 2 + 1)});
+            ids.push_back(g);
             poff.push_back((int64_t)seg.size());
-            kmax = std::max<int>(kmax, (int)tcnt[g]);
         }
-        MM_TRY(sum_rows(czt_ids, poff, d_kid_c, d_poff_c));
+        MM_TRY(sum_rows(ids, poff, d_kid_c, d_poff_c));
         MM_TRY(d_seg.alloc(seg.size()));
         MM_TRY(d_clen.alloc(lens.size()));
         MM_TRY(d_chirp.alloc(lens.size() * kCz));
@@ -1407,8 +1425,8 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
                            pl->opts.f_samp, d_tw.p, (const double2*)d_chirp.p, kmax, d_part_c.p,
                            what);
         MM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, nf), dim3(256), 0, st, d_kid_c.p,
-                           d_klen, d_toff, d_tcnt, d_part_c.p, kmax, d_poff_c.p, lam,
+        hipLaunchKernelGGL(k_taps_sum, dim3((kmax + 255) / 256, (unsigned)ids.size()), dim3(256), 0,
+                           st, d_kid_c.p, d_klen, d_toff, d_tcnt, d_part_c.p, kmax, d_poff_c.p, lam,
                            pl->opts.window, d_t.p);
         MM_HIP(hipGetLastError());
     }
