@@ -33,9 +33,8 @@ __device__ __forceinline__ void scan_step(T (&acc)[NV], bool take) {
 
 // Wave-level segmented reduction over pixel-sorted samples.
 //
-// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., counted from a
-// multiple of 64 at or below the first (32-bit positions, see mm_pos.h: the caller moves its
-// pointers there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
+// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., at 32-bit
+// positions from a base sample (see mm_pos.h: the caller moves its pointers there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
 // (e < E), loaded with aligned vector loads so E gathers are in flight per lane.
 // Each lane first sums its own samples segment by segment, then one segmented
 // inclusive scan over the 64 lane summaries (flag: the lane holds a segment
@@ -216,8 +215,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 8 && NS == 3 ? 6 : 8) void k_scat
     const WaveRange wr = rng[w];
     if (wr.p0 >= wr.p1) return;
     if (mask && !mask[wr.prob]) return;
-    // positions from a multiple of 64
-    const int64_t c0 = wr.i0 & ~(int64_t)63;
+    const int64_t c0 = range_base(wr.i0, wr.i1);
     const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;
@@ -350,8 +348,7 @@ __global__ __launch_bounds__(256) void k_scatter_cols(
     if (wr.p0 >= wr.p1) return;
     const int64_t q0 = ooff[b], n_vec = (ooff[b + 1] - q0) * NS;
     float* const azb = az + blk_off[b] + (int64_t)k0 * n_vec - q0 * NS;  // pixel q0 at 0
-    // positions from a multiple of 64
-    const int64_t c0 = wr.i0 & ~(int64_t)63;
+    const int64_t c0 = range_base(wr.i0, wr.i1);
     const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;
@@ -488,7 +485,7 @@ __global__ __launch_bounds__(256) void k_bj_build(
     // the interval [jlo, jhi) and t_0 of its last sample and searches only outside it
     int64_t jlo = 0, jhi = 0;
     double dj = 0.0;
-    const int64_t c0 = wr.i0 & ~(int64_t)63;  // positions from a multiple of 64
+    const int64_t c0 = range_base(wr.i0, wr.i1);
     const pos_t i0 = (pos_t)(wr.i0 - c0), i1 = (pos_t)(wr.i1 - c0);
     perm += c0;
     ws += 2 * c0;

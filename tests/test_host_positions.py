@@ -17,19 +17,22 @@ using namespace mm;
 int main() {
     const int E = 4;
     for (int64_t n : {(int64_t)1, (int64_t)257, ((int64_t)1 << 30) + 5, ((int64_t)1 << 31) - 1}) {
-        for (int64_t at : {(int64_t)0, (int64_t)63}) {  // the range's first sample after its base
-            const pos_t i0 = (pos_t)at, i1 = (pos_t)(at + n);
+        for (int64_t at : {(int64_t)0, (int64_t)63, ((int64_t)1 << 31) + 17}) {  // first sample
+            const int64_t base = range_base(at, at + n);
+            if (base & 63) return 9;
+            const pos_t i0 = (pos_t)(at - base), i1 = (pos_t)(at + n - base);
+            if (i0 + base != at || i1 + base != at + n) return 10;
             int64_t want = at & ~(int64_t)(E - 1), chunks = 0;
             for (pos_t c = first_chunk(i0, E); c < i1; c = next_chunk(c, E), want += 64 * E) {
                 if (++chunks > n / (64 * E) + 2) return 1;                 // does not end
-                if ((int64_t)c != want) return 2;
-                if ((int64_t)next_chunk(next_chunk(c, E), E) != want + 128 * E) return 3;
+                if (c + base != want) return 2;
+                if (next_chunk(next_chunk(c, E), E) + base != want + 128 * E) return 3;
                 for (int lane : {0, 1, 63}) {
                     const pos_t b = lane_base(c, lane, E);
-                    if ((int64_t)b != want + lane * E) return 4;
-                    if ((int64_t)(b + E) != want + lane * E + E) return 5;
-                    if (weight_index(b) != 2 * (want + lane * E)) return 6;
-                    if (weight_index(b) * (int64_t)sizeof(double) != 16 * (want + lane * E)) return 7;
+                    if (b + base != want + lane * E) return 4;
+                    if ((b >> 6) + (base >> 6) != (want + lane * E) >> 6) return 5;
+                    if ((b & 63) != ((want + lane * E) & 63)) return 6;
+                    if (weight_index(b + E) + 2 * base != 2 * (want + lane * E + E)) return 7;
                 }
             }
             if (want < at + n) return 8;
