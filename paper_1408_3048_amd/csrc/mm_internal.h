@@ -109,7 +109,7 @@ struct FftTiling {
     int64_t n_tiles = 0;
     DBuf<TileRec> tiles;     // [n_tiles]
     DBuf<double> H64;        // [n_kern][M+1] kernel spectrum / n_r, FP64 operator; paired:
-                             // [n_kern][n_r] in the order of k_toeplitz_pair
+                             // the same values in the order of k_toeplitz_pair, a few twice
     DBuf<float> H32;         // same, FP32 operator
     DBuf<double> tw64;       // [n_r/2][2] exp(-2 pi i q / n_r)
     DBuf<float> tw32;

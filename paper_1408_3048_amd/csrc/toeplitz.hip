@@ -194,8 +194,8 @@ struct ToepArgs {
     int y_f64;
     int mode;             // 0 map IQU, 1 map I, 2 TOD FP64, 3 TOD FP32
     T* z;
-    const T* H;           // [n_kern][M + 1]
-    const T* tw;          // [M][2]
+    const T* H;           // [n_kern][M + 1], or [n_kern][PairSpectrum::LEN]
+    const T* tw;          // [M][2], or RegFft's table
     const TileRec* tiles;
     int lam;
     int64_t n_tiles;          // tiles of the launch (blocks are mapped to tiles XCD-major)
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
 // transform is RegFft's: a thread loads point t + NT i of both windows straight into its
 // registers (samples of consecutive threads are consecutive), and stores its results from
 // there; LDS carries the two exchanges each way alone.  H is stored in the order the threads
-// hold the bit-reversed spectrum, two values per thread and load.
+// hold the bit-reversed spectrum (PairSpectrum).
 //
 // What bounded the LDS-resident FP64 tile was the latency of its passes at 2 waves per SIMD
 // (a complex buffer of 64 KB per tile); here 4 are resident.  N^-1 of a TOD / N^-1 P x, in us,
@@ -613,6 +613,30 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
 // The same kernel in FP32 (32 points per thread) gained nothing at 16384 points (raster of
 // 2^24: 94.5 / 96.5 us, ring scan of 2^25: 229 / 235) and lost at 8192 and below 2^23 samples
 // (half as many workgroups): FP32 keeps the LDS-resident tile.
+
+// The spectrum H (real, H(f) = H(N - f)) as k_toeplitz_pair's threads read it.  Position p > 0 of
+// the bit-reversed spectrum and its mirror 3 2^m - 1 - p in [2^m, 2^(m+1)) hold f and N - f, so
+// thread t > 1 of [2^k, 2^(k+1)) holds the values of thread 3 2^k - 1 - t in reverse: a row of R
+// values is stored for one of the two, value i of row r at [i][r].
+template <int LOGN>
+struct PairSpectrum {
+    static constexpr int R = RegFft<LOGN>::R, NT = RegFft<LOGN>::NT, ROWS = NT / 2 + 1,
+                         LEN = R * ROWS;
+    static __device__ __forceinline__ int top(int t) { return 31 - __clz(t); }
+    // whether thread t reads its mirror's row, backwards
+    static __device__ __forceinline__ bool mirrored(int t) {
+        return t > 1 && ((t >> (top(t) - 1)) & 1);
+    }
+    static __device__ __forceinline__ int row(int t) {
+        if (t < 2) return t;
+        const int k = top(t), u = mirrored(t) ? (3 << k) - 1 - t : t;
+        return u - (1 << (k - 1)) + 1;
+    }
+    // the thread whose values row r holds
+    static __device__ __forceinline__ int thread(int r) {
+        return r < 2 ? r : r - 1 + (1 << top(r - 1));
+    }
+};
 
 // vr[i], vi[i] = sample t + NT i of the two windows, 0 outside their interval, BP samples at a
 // time alternating between the windows; nz: whether any is nonzero
@@ -779,7 +803,7 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
     // now by less than 1e-12 at any ratio; the norms take the place of the vote on samples that
     // are not finite, and solves of 2^22 samples take 8.73 ms for 8.68, gradients 12.76 for 12.66
     __shared__ float red[2 * (NT / 64)];
-    int e[2] = {0, 0};  // the windows are scaled by 2^-e
+    int e[2] = {0, 0};  // powers of two that are taken out of the windows
     float q[2];
     pair_norms<R, NT>(vr, vi, red, q);
     const auto in_range = [](float x) { return x > 1e-30f && x < 1e36f; };
@@ -815,7 +839,8 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
         }
         pair_norms<R, NT>(vr, vi, red, q);
     }
-    {
+    double back = 1.0;  // the second window's factor after the transform
+    if (!fixed[0] && !fixed[1]) {
         int f[2];  // the norms are in [2^(f-1), 2^f)
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
@@ -823,14 +848,11 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
             (void)frexpf(q[w], &x);
             f[w] = (x + 1) >> 1;
         }
-        if (f[0] != f[1] && !fixed[0] && !fixed[1]) {
+        if (f[0] != f[1]) {
+            const double to = ldexp(1.0, f[0] - f[1]);
+            back = ldexp(1.0, f[1] - f[0]);
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                vr[i] = ldexp(vr[i], -f[0]);
-                vi[i] = ldexp(vi[i], -f[1]);
-            }
-            e[0] += f[0];
-            e[1] += f[1];
+            for (int i = 0; i < R; ++i) vi[i] *= to;
         }
     }
     // without SKIPZ always taken: the transform in a block of its own keeps the compiler from
@@ -841,17 +863,23 @@ __global__ __launch_bounds__(RegFft<LOGN>::NT, 4) void k_toeplitz_pair(ToepArgs<
     if (go) {
         F::forward(vr, vi, s, a.tw, t);
         F::pin(vr, vi);
-        const double2* h = reinterpret_cast<const double2*>(a.H + (int64_t)tr.kern * F::N);
+        using S = PairSpectrum<LOGN>;
+        const bool mir = S::mirrored(t);
+        const double* h =
+            a.H + (int64_t)tr.kern * S::LEN + S::row(t) + (mir ? (R - 1) * S::ROWS : 0);
+        const int step = mir ? -S::ROWS : S::ROWS;
 #pragma unroll
-        for (int q = 0; q < R / 2; ++q) {
-            const double2 hv = h[q * NT + t];
-            vr[2 * q] *= hv.x;
-            vi[2 * q] *= hv.x;
-            vr[2 * q + 1] *= hv.y;
-            vi[2 * q + 1] *= hv.y;
+        for (int i = 0; i < R; ++i) {
+            const double hv = h[i * step];
+            vr[i] *= hv;
+            vi[i] *= hv;
         }
         F::pin(vr, vi);
         F::inverse(vr, vi, s, a.tw, F::fresh(t));
+        if (back != 1.0) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) vi[i] *= back;
+        }
         if (e[0] | e[1]) {
 #pragma unroll
             for (int i = 0; i < R; ++i) {
@@ -893,17 +921,16 @@ __global__ void k_twiddles_pair(int logn, int logr, double* __restrict__ tw) {
     }
 }
 
-// the spectra H(f) / N in the order of k_toeplitz_pair's threads: value e of pair q of thread t
-// is position R t + 2 q + e of the bit-reversed spectrum
-__global__ void k_spec_pair(const double* __restrict__ Hraw, int logn, int logr, double scale,
+// the spectrum H(f) / N of kernel blockIdx.x
+template <int LOGN>
+__global__ void k_spec_pair(const double* __restrict__ Hraw, double scale,
                             double* __restrict__ out) {
-    const int n = 1 << logn, r = 1 << logr, nt = n / r;
-    const double* h = Hraw + (int64_t)blockIdx.y * (n / 2 + 1);
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
-        const int e = x & 1, t = (x >> 1) % nt, q = (x >> 1) / nt;
-        const int p = r * t + 2 * q + e;
-        const int f = (int)(__builtin_bitreverse32((uint32_t)p) >> (32 - logn));
-        out[(int64_t)blockIdx.y * n + x] = h[f <= n / 2 ? f : n - f] * scale;
+    using S = PairSpectrum<LOGN>;
+    constexpr int n = 1 << LOGN;
+    const double* h = Hraw + (int64_t)blockIdx.x * (n / 2 + 1);
+    for (int x = threadIdx.x; x < S::LEN; x += blockDim.x) {
+        const int f = rev_bits<LOGN>(S::R * S::thread(x % S::ROWS) + x / S::ROWS);
+        out[(int64_t)blockIdx.x * S::LEN + x] = h[f <= n / 2 ? f : n - f] * scale;
     }
 }
 
@@ -1667,7 +1694,8 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
     }
     const double scale = 1.0 / (double)ft.n_r;
     if (ft.paired) {
-        MM_TRY(ft.H64.alloc((size_t)nk * ft.n_r));
+        MM_TRY(ft.H64.alloc((size_t)nk *
+                            (logm == 11 ? PairSpectrum<12>::LEN : PairSpectrum<13>::LEN)));
     } else if (fp64) {
         MM_TRY(ft.H64.alloc((size_t)nk * (M + 1)));
     } else {
@@ -1682,8 +1710,12 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
         MM_TRY(ft.tw64.alloc(2 * ntw));
         hipLaunchKernelGGL(k_twiddles_pair, dim3((ntw + 255) / 256), dim3(256), 0, st, logm + 1, lr,
                            ft.tw64.p);
-        hipLaunchKernelGGL(k_spec_pair, dim3((unsigned)(ft.n_r / 256), (unsigned)nk), dim3(256), 0,
-                           st, d_h.p, logm + 1, lr, scale, ft.H64.p);
+        if (logm == 11)
+            hipLaunchKernelGGL(k_spec_pair<12>, dim3((unsigned)nk), dim3(256), 0, st, d_h.p, scale,
+                               ft.H64.p);
+        else
+            hipLaunchKernelGGL(k_spec_pair<13>, dim3((unsigned)nk), dim3(256), 0, st, d_h.p, scale,
+                               ft.H64.p);
     }
     MM_HIP(hipGetLastError());
     std::vector<double> hmin(nk);
