@@ -485,19 +485,28 @@ __device__ __forceinline__ bool load_window(const ToepArgs<T>& a, const CBuf<T>&
 // the butterflies and gathers would spill (4 waves = 128 VGPRs for FP32, 3 = 170
 // for FP64): the register budget the compiler must meet so that LDS bounds occupancy
 template <typename T, int LOGM, int NT>
-constexpr int tile_waves_per_simd(int table_bytes = 0) {
-    constexpr int bytes = 2 * (1 << LOGM) * (int)sizeof(T);
-    const int w = (160 * 1024) / (bytes + table_bytes) * (NT / 64) / 4;
+constexpr int tile_waves_per_simd() {
+    constexpr int blocks = (160 * 1024) / (2 * (1 << LOGM) * (int)sizeof(T));
+    constexpr int w = blocks * (NT / 64) / 4;
     constexpr int cap = sizeof(T) == 4 ? 4 : 3;
     return w < 1 ? 1 : (w > cap ? cap : w);
 }
-// the LDS twiddle table is used where it leaves the tile's occupancy unchanged
+// the LDS twiddle table is used where it leaves the number of resident tiles unchanged, by LDS and
+// by the 32 waves that a CU holds.  The 8192-point FP32 tile, 5 a CU without the table and 4 with
+// it, takes, with / without: N^-1 of a TOD of 2^20 samples 11.2 / 11.1 us, of 48 problems (7.3e6
+// samples) 28.6 / 28.1, A x 90.2 / 90.3
 template <typename T, int LOGM, int NT>
 constexpr bool ltw_enabled() {
-    return ltw_total(LOGM) > 0 &&
-           tile_waves_per_simd<T, LOGM, NT>(2 * ltw_total(LOGM) * (int)sizeof(T)) ==
-               tile_waves_per_simd<T, LOGM, NT>();
+    constexpr int cu = 160 * 1024, wmax = 32 / (NT / 64);
+    constexpr int bytes = 2 * (1 << LOGM) * (int)sizeof(T);
+    constexpr int tbytes = 2 * ltw_total(LOGM) * (int)sizeof(T);
+    constexpr int b0 = cu / bytes < wmax ? cu / bytes : wmax;
+    constexpr int b1 = cu / (bytes + tbytes) < wmax ? cu / (bytes + tbytes) : wmax;
+    return ltw_total(LOGM) > 0 && b0 == b1;
 }
+static_assert(ltw_enabled<float, 11, 256>() && !ltw_enabled<float, 12, 256>() &&
+                  ltw_enabled<float, 13, 512>(),
+              "8 tiles of 4096 points fit a CU with the table, 4 of 8192 instead of 5, 2 of 16384");
 
 // threads of a tile: one radix-16 group per thread and pass
 template <int LOGM>
@@ -552,7 +561,7 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
     if constexpr (LTW && !SKIPZ) fill_ltw<T, LOGM, NT>(a.tw, lt);
     // the shortest tiles, a launch of which is a chain of latencies, have registers to load the
     // spectrum's values with the window (with the tile in one record, N^-1 P of 2^14 samples
-    // 9.5 -> 8.9 us; the record alone, 2^20 samples FP32 14.7 -> 13.9 and FP64 24.8 -> 24.3)
+    // 9.5 -> 8.9 us; the record alone, 2^20 samples FP64 24.8 -> 24.3)
     constexpr bool EARLY = LOGM == 10;
     [[maybe_unused]] std::conditional_t<EARLY, SpectrumValues<T, LOGM, NT>, Unused> early(
         a.H + (int64_t)tr.kern * (M + 1), a.tw);
