@@ -1292,7 +1292,7 @@ int64_t count_tiles(const std::vector<int64_t>& off, int64_t lmax, bool paired) 
 
 // FP64 lengths n_r = 2^(l + 1) whose tiles go in pairs (k_toeplitz_pair): 4096 and 8192.  2048
 // points serve short intervals, often of one tile; 16384 points would need 128 KB of LDS, one
-// workgroup per CU, as the LDS-resident tile does, and are taken for lambda > 3072
+// workgroup per CU, as the LDS-resident tile does, and are taken from lambda of about 2900
 bool pair_length(bool fp64, int l) { return fp64 && (l == 11 || l == 12); }
 
 }  // namespace
@@ -1572,24 +1572,33 @@ int build_tiling(mm_plan_t pl, FftTiling& ft, bool fp64, int n_r_request) {
         }
         logm = l;
     } else {
-        // smallest modelled time: tiles x n_r x (log2 n_r + 4), doubled for a tile whose
-        // LDS leaves room for only one resident tile per CU (160 KB): a second tile hides
-        // the other's window load (measured: 32768-point FP32 tiles at lambda = 4096 take
-        // 1.27x the time of 16384-point ones, for 0.72x the modelled work).  Fewer tiles than
-        // CUs count as one tile per CU: such a launch takes the time of one tile, so the
-        // shorter length wins (A x of 2^18 intensity samples, lambda = 1024, FP64: 24.2 us
-        // with 128 tiles of 4096 points, 32.9 with 48 of 8192; 2^20 IQU samples, lambda = 2048,
-        // FP32: 32.0 us with 256 tiles of 8192, 34.9 with 96 of 16384)
+        // Smallest modelled time: workgroups x points x (log2 n_r + 4), a pair of FP64 tiles being
+        // one workgroup of 2 n_r points; fewer workgroups than CUs count as one per CU, since such a
+        // launch takes the time of one.  Doubled
+        //  - in FP32 for a tile whose LDS leaves room for only one resident tile per CU (160 KB): a
+        //    second tile hides the other's window load (32768-point tiles at lambda = 4096 take
+        //    1.27x the time of 16384-point ones, for 0.72x the modelled work);
+        //  - in FP64 for the lengths that do not go in pairs: N^-1 of a TOD of 2^24 samples
+        //    takes 11.4 ns per tile of 2048 points, 24.3 per pair of 4096, 58 of 8192 and 87 per tile
+        //    of 16384: 2.0, 1, 1.12 and 1.6 times the model's; at 2^22 samples, where a CU takes two
+        //    tiles of 16384 after each other, these count 2.1.
+        // Pairs of 8192 points count 6% more (as in A x; N^-1 12%).  A x in us: 2^18 samples, lambda
+        // = 512: 2048 points 17.5, 4096 21.4; 2^18, lambda = 1024: 64 pairs of 4096 points 21.3, 32 of
+        // 8192 29.4; 2^21, lambda = 512: 4096 44.6, 8192 46.4; 2^24, lambda = 512: 4096 233, 8192 240;
+        // 2^22, lambda = 2700: 8192 91, 16384 95.7, lambda = 2850: 99.3, 96.0; 2^24, lambda = 2800:
+        // 325, 334, lambda = 3072: 357, 336.  FP32, 2^20, lambda = 2048: 32.0 with 256 tiles of 8192,
+        // 34.9 with 96 of 16384
         double best = 0.0;
         for (int l = kMinLogM; l <= maxlogm; ++l) {
             const int64_t nr = (int64_t)2 << l;
             const int64_t lmax = nr - 2 * (int64_t)lam;
             if (lmax < nr / 4) continue;
-            const int64_t tile_lds = nr * (fp64 ? 8 : 4);
-            const double resident = (160 * 1024) / tile_lds >= 2 ? 1.0 : 2.0;
-            const double tiles = (double)std::max<int64_t>(
-                count_tiles(pl->h_off, lmax, pair_length(fp64, l)), kCus);
-            const double cost = tiles * (double)nr * (l + 5) * resident;
+            const bool paired = pair_length(fp64, l);
+            const int64_t wgs = count_tiles(pl->h_off, lmax, paired) / (paired ? 2 : 1);
+            double factor = l == kMaxLogM32 || (fp64 && !paired) ? 2.0 : 1.0;
+            if (fp64 && l == kMaxLogM64) factor = 2.1;
+            if (paired) factor = l == 12 ? 2.12 : 2.0;  // 2 n_r points
+            const double cost = (double)std::max<int64_t>(wgs, kCus) * (double)nr * (l + 5) * factor;
             if (logm == 0 || cost < best) {
                 best = cost;
                 logm = l;
