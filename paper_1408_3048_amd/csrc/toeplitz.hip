@@ -1164,11 +1164,15 @@ __global__ __launch_bounds__(NT) void k_taps_czt(const CztSeg* __restrict__ seg,
 
 constexpr int kPlanLogM = 13;  // plan-time FP64 FFTs: n_r = 16384 real points
 constexpr int kPlanNT = 512;
-// taps by chirp transforms: from 4096 samples, for lags that leave a segment at least a
-// quarter of the transform.  Plans of 256 intervals of about 4097 samples take, direct /
-// chirps, 1.33 / 1.06 ms at 2049 lags and 1.04 / 1.03 at 65, of 2001 samples 1.00 / 0.98; a
-// single interval of 4097 samples takes 0.82 / 0.85 and of 8195 0.88 / 0.88
-constexpr int64_t kCztMinLen = 4096, kCztMaxLag = 6144;
+// Taps by chirp transforms: for lags that leave a segment at least a quarter of the transform,
+// from 4096 samples with 512 lags or more and from 6144 with fewer (by the interval alone, so that
+// an interval's taps do not depend on the others).  A plan in us, direct / chirps, of one interval,
+// of 16 and of 256: 4097 samples and 64 lags 492 / 498, 540 / 552, 1300 / 1327; 2048 lags 510 / 517,
+// 554 / 563, 1665 / 1400; 6001 samples and 64 lags 514 / 502, 582 / 571, 1650 / 1650; 2048 lags 535 /
+// 517, 600 / 590, 2160 / 1720; 12289 samples and 64 lags 597 / 514, 722 / 646, 2875 / 2760.
+// mm_tap_derivatives, three transforms: one interval of 4097 samples 250 / 320-350, of 6001 316 /
+// 325-360, of 8195 396 / 335-370; 256 of 4097 with 512 lags 880 / 820.
+constexpr int64_t kCztMinLen = 4096, kCztMinLenFew = 6144, kCztFewLags = 512, kCztMaxLag = 6144;
 
 template <typename T, int LOGM>
 int launch_logm(const ToepArgs<T>& a_in, int64_t n_tiles, hipStream_t st) {
@@ -1342,7 +1346,8 @@ int kernel_taps_dev(mm_plan_t pl, int what, DBuf<double>& d_t, std::vector<int64
         const int64_t n = pl->h_kern_len[g];
         const int64_t K = std::min<int64_t>(lam, n - 1);
         const bool by_fft = n % kNs == 0 && K < kNs / 2;
-        const bool by_czt = !by_fft && n >= kCztMinLen && K <= kCztMaxLag;
+        const bool by_czt =
+            !by_fft && n >= (K < kCztFewLags ? kCztMinLenFew : kCztMinLen) && K <= kCztMaxLag;
         if (by_fft) fft_ids.push_back(g);
         else if (by_czt) czt_ids.push_back(g);
         else direct = true;

@@ -51,3 +51,9 @@ def test_taps_of_more_lengths_than_one_launch_holds(lam, most):
 def test_taps_of_an_interval_of_many_segments():
     """2^23 + 3 samples at lambda = 6144: 2049 segments of 2048 frequencies, three a row."""
     _taps(np.array([(1 << 23) + 3, 5000]), 6144, [0, 1])
+
+
+@pytest.mark.parametrize("lam", [511, 512])
+def test_taps_on_either_side_of_the_chirps_lines(lam):
+    """Chirp transforms from 4096 samples with 512 lags, from 6144 with fewer: the same bar."""
+    _taps(np.array([4095, 4096, 4097, 6143, 6144, 6145]), lam, range(6))
