@@ -446,11 +446,12 @@ int full_iteration(mm_plan_t pl, const EngineArgs& ea, double* x, double* r, dou
     // P^T leaves the partials of p^T q of the problems whose ranges have slots
     MM_TRY(ea.op32 ? apply_A32_tag(pl, p, q, c.mask, tag, true)
                    : apply_A64_tag(pl, p, q, c.mask, tag, true));
-    MM_TRY(prof_begin(pl, MM_K_VEC, tag));
-    if (pl->n_slotted < pl->n_prob)
+    const bool dots = pl->n_slotted < pl->n_prob, bj = ea.pc == MM_BJ;
+    if (dots || !bj) MM_TRY(prof_begin(pl, MM_K_VEC, tag));
+    if (dots)
         MM_TRY(vec_dot(pl, p, q, kSlotPQ, c, pl->n_slotted > 0 ? pl->wave_off.p : nullptr));
-    if (ea.pc == MM_BJ) {
-        MM_TRY(prof_end(pl, MM_K_VEC));
+    if (bj) {
+        if (dots) MM_TRY(prof_end(pl, MM_K_VEC));
         MM_TRY(prof_begin(pl, MM_K_PRECOND, tag));
         MM_TRY(pcg_update_xr_bj(pl, x, r, z, p, q, c));
         MM_TRY(prof_end(pl, MM_K_PRECOND));
