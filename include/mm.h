@@ -313,6 +313,14 @@ int mm_fft_lengths(mm_plan_t plan, int* n_r_f64, int* n_r_f32);
  * value), or a negative status. */
 int mm_pt_range(mm_plan_t plan);
 
+/* Samples per P^T work range of every problem in the passes that built A Z_S, into host
+ * host_out (at most cap values); returns the number of problems, 0 for a plan without Z_S, or a
+ * negative status. */
+int mm_az_pt_ranges(mm_plan_t plan, int32_t* host_out, int cap);
+
+/* Captured iteration graphs that the plan holds (opts.graph), or a negative status. */
+int mm_graph_count(mm_plan_t plan);
+
 /* ----- adjoint (gradients of a loss of the map) ----- */
 
 /* Lag cross-correlations per stationary interval j of two TOD vectors u, v (device FP64

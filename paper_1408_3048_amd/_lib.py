@@ -38,7 +38,7 @@ EXPORTED = [
     "mm_problem_pixels", "mm_coarse_problem_columns", "mm_fft_lengths", "mm_lag_correlations",
     "mm_tap_derivatives", "mm_adjoint", "mm_coarse_from_krylov", "mm_lanczos_ritz",
     "mm_coarse_kind", "mm_coarse_ritz_values", "mm_coarse_dense_columns", "mm_precond_adef2",
-    "mm_gemm_tn_f64_noalloc", "mm_pt_range",
+    "mm_gemm_tn_f64_noalloc", "mm_pt_range", "mm_az_pt_ranges", "mm_graph_count",
 ]
 
 
@@ -108,6 +108,8 @@ def load():
         "mm_gemm_tn_f64": (I, [P, P, P, I64, I32, I32, P]),
         "mm_gemm_tn_f64_noalloc": (I, [P, P, P, I64, I32, I32, P]),
         "mm_pt_range": (I, [P]),
+        "mm_az_pt_ranges": (I, [P, P, I]),
+        "mm_graph_count": (I, [P]),
         "mm_profile": (I, [P, I]),
         "mm_profile_read": (I, [P, I, ctypes.POINTER(I64), ctypes.POINTER(D)]),
         "mm_last_error": (ctypes.c_char_p, []),
@@ -337,6 +339,19 @@ class Plan:
     def pt_range(self):
         """Samples per P^T work range of the plan."""
         v = self._lib.mm_pt_range(self._h)
+        check(min(v, 0))
+        return v
+
+    def az_pt_ranges(self):
+        """Samples per P^T work range of every problem in the A Z_S build (empty without one)."""
+        out = np.zeros(self.n_problems, dtype=np.int32)
+        n = self._lib.mm_az_pt_ranges(self._h, out.ctypes.data_as(ctypes.c_void_p), out.size)
+        check(min(n, 0))
+        return out[:n]
+
+    def graph_count(self):
+        """Captured iteration graphs that the plan holds."""
+        v = self._lib.mm_graph_count(self._h)
         check(min(v, 0))
         return v
 

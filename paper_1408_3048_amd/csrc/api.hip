@@ -1438,6 +1438,29 @@ int mm_pt_range(mm_plan_t pl) {
     return (int)pl->pt_range;
 }
 
+int mm_az_pt_ranges(mm_plan_t pl, int32_t* host_out, int cap) {
+    clear_error();
+    if (!pl || (!host_out && cap > 0)) {
+        set_error("NULL argument");
+        return MM_ERR_ARG;
+    }
+    const int n = (int)pl->az_pt_ranges.size();
+    for (int b = 0; b < n && b < cap; ++b) host_out[b] = pl->az_pt_ranges[b];
+    return n;
+}
+
+int mm_graph_count(mm_plan_t pl) {
+    clear_error();
+    if (!pl) {
+        set_error("plan is NULL");
+        return MM_ERR_ARG;
+    }
+    int n = 0;
+    for (auto& row : pl->gexec)
+        for (auto& g : row) n += g != nullptr;
+    return n;
+}
+
 int mm_profile(mm_plan_t pl, int enable) {
     clear_error();
     if (!pl) {

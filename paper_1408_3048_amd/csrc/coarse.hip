@@ -1428,6 +1428,7 @@ int build_coarse(mm_plan_t pl) {
     const bool mixed = pl->opts.precision == MM_MIXED;
     const int64_t pt_keep = pl->pt_range;  // the plan's P^T range, restored after A Z
     MM_TRY(build_wave_ranges(pl, kAzPtRange, kAzMinWaves));
+    pl->az_pt_ranges = pl->pt_ranges;
     DBuf<double> azd;
     DBuf<float> azf;
     if (mixed) MM_TRY(azf.alloc((size_t)azd_off[B]));

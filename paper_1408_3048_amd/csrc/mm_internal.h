@@ -251,6 +251,8 @@ struct mm_plan_s {
     std::vector<int64_t> h_soff;        // [B+1] first padded sorted position of every problem
     std::vector<int64_t> h_pn;          // [B] samples of every problem
     int64_t pt_range = 512;             // samples per P^T work range
+    std::vector<int32_t> pt_ranges;     // [B] the same of every problem
+    std::vector<int32_t> az_pt_ranges;  // [B] of the passes that built A Z_S (empty: none did)
     int64_t n_sorted = 0;               // padded sorted length (problems start 8-aligned)
     mm::DBuf<int64_t> ooff;             // [B+1] compact pixel offsets
     mm::DBuf<int32_t> eblk, pblk;       // [B+1] vector-kernel block offsets (elements, pixels)

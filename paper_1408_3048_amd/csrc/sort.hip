@@ -624,6 +624,7 @@ int build_wave_ranges(mm_plan_t pl, int64_t per_wave, int64_t min_waves) {
     pl->n_slotted = 0;
     for (int b = 0; b < B; ++b) pl->n_slotted += woff[b + 1] - woff[b] <= kVecBlocks;
     pl->pt_range = per_wave;
+    pl->pt_ranges.assign(pw.begin(), pw.end());
     DBuf<int64_t> d_pw;
     MM_TRY(d_pw.alloc(B));
     MM_HIP(hipMemcpyAsync(d_pw.p, pw.data(), B * 8, hipMemcpyHostToDevice, st));
