@@ -235,17 +235,16 @@ __global__ void k_cols_to_maps(const int32_t* __restrict__ ucol, const int32_t* 
 }
 
 // copy problem lp[y]'s slice of the map vector y into column `col` of its AZ block
-template <typename TA>
 __global__ void k_store_az(const int32_t* __restrict__ lp, const double* __restrict__ y,
                            const int64_t* __restrict__ ooff, int ns,
                            const int64_t* __restrict__ blk_off, int32_t col,
-                           TA* __restrict__ az) {
+                           double* __restrict__ az) {
     const int32_t b = lp[blockIdx.y];
     const int64_t v0 = ooff[b] * ns, n = (ooff[b + 1] - ooff[b]) * ns;
-    TA* dst = az + blk_off[b] + (int64_t)col * n;
+    double* dst = az + blk_off[b] + (int64_t)col * n;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = (TA)y[v0 + i];
+        dst[i] = y[v0 + i];
 }
 
 // copy n[c] values from src + so[c] to dst + d_o[c] for every column c = blockIdx.y; with
@@ -804,17 +803,16 @@ __global__ void k_f32_to_f64(const float* __restrict__ a, double* __restrict__ b
 }
 
 // column `col` of the dense block of problem lp[y] into its slice of a zeroed map vector
-template <typename TA>
-__global__ void k_zd_to_vec(const int32_t* __restrict__ lp, const TA* __restrict__ zd,
+__global__ void k_zd_to_vec(const int32_t* __restrict__ lp, const double* __restrict__ zd,
                             const int64_t* __restrict__ ooff, int ns,
                             const int64_t* __restrict__ blk_off, int32_t col,
                             double* __restrict__ out) {
     const int32_t b = lp[blockIdx.y];
     const int64_t v0 = ooff[b] * ns, n = (ooff[b + 1] - ooff[b]) * ns;
-    const TA* src = zd + blk_off[b] + (int64_t)col * n;
+    const double* src = zd + blk_off[b] + (int64_t)col * n;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
-        out[v0 + i] = (double)src[i];
+        out[v0 + i] = src[i];
 }
 
 // columns k0 .. k0 + gridDim.z of every problem's dense block into maps side by side, as N^-1 P
@@ -1528,7 +1526,7 @@ int build_coarse(mm_plan_t pl) {
                 const int64_t lo_k = lo;
                 MM_TRY(layer_maps(k, 1));
                 MM_TRY(apply_A64_sparse_i(pl, zc.p, tmp.p, on.p + (int64_t)k * K));
-                hipLaunchKernelGGL(k_store_az<double>, dim3(sgx, nl), dim3(256), 0, st,
+                hipLaunchKernelGGL(k_store_az, dim3(sgx, nl), dim3(256), 0, st,
                                    lprob.p + lo_k, (const double*)tmp.p, pl->ooff.p, (int)ns,
                                    (const int64_t*)d_azd_off.p, k, azd.p);
                 MM_HIP(hipGetLastError());
@@ -1946,12 +1944,12 @@ int build_coarse_dense(mm_plan_t pl, const double* basis, int64_t basis_stride,
         for (int32_t k = 0; k < r_max; ++k) {
             const dim3 g(sgx, lcnt[k]);
             MM_HIP(hipMemsetAsync(x.p, 0, nv * 8, st));
-            hipLaunchKernelGGL(k_zd_to_vec<double>, g, dim3(256), 0, st, lprob.p + lo,
+            hipLaunchKernelGGL(k_zd_to_vec, g, dim3(256), 0, st, lprob.p + lo,
                                (const double*)zd64.p, pl->ooff.p, (int)ns,
                                (const int64_t*)dzoff.p, k, x.p);
             MM_HIP(hipGetLastError());
             MM_TRY(apply_A64_sparse(pl, x.p, y.p));
-            hipLaunchKernelGGL(k_store_az<double>, g, dim3(256), 0, st, lprob.p + lo,
+            hipLaunchKernelGGL(k_store_az, g, dim3(256), 0, st, lprob.p + lo,
                                (const double*)y.p, pl->ooff.p, (int)ns,
                                (const int64_t*)dzoff.p, k, az64.p);
             MM_HIP(hipGetLastError());

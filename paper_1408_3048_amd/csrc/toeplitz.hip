@@ -358,10 +358,8 @@ __device__ __forceinline__ bool load_window(const ToepArgs<T>& a, const CBuf<T>&
                                             int64_t base, int win, int64_t lo, int64_t hi) {
     constexpr int NR = 2 << LOGM;
     constexpr int PER = NR / NT;
-    // gathers in flight per thread: 8 for the IQU map gather (its registers bound the
-    // occupancy), 16 otherwise
-    constexpr int BMAX = MODE == 0 ? 8 : 16;
-    constexpr int B = PER < BMAX ? PER : BMAX;
+    // samples in flight per thread (the IQU map gather has batches of its own)
+    constexpr int B = PER < 16 ? PER : 16;
     static_assert(PER % B == 0, "tile must split into batches");
     static_assert(NT % 2 == 0, "even thread count");
     // point (tid + c NT) / 2 = tid / 2 + c NT / 2 with bit-disjoint terms
@@ -376,7 +374,7 @@ __device__ __forceinline__ bool load_window(const ToepArgs<T>& a, const CBuf<T>&
     if constexpr (MODE == 0) {
         // IQU map gather, software-pipelined: the indices and weights of batch k + 1 are
         // loaded while the map gathers of batch k are in flight, so a batch waits for one
-        // memory latency instead of two (the values are those of the plain loop below);
+        // memory latency instead of two;
         // batches of 8 samples in FP32, 4 in FP64 (registers)
         typedef typename std::conditional<sizeof(T) == 4, float4, double4>::type T4;
         typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type T2;
@@ -436,26 +434,7 @@ __device__ __forceinline__ bool load_window(const ToepArgs<T>& a, const CBuf<T>&
             rr[u] = (uint32_t)(ok[u] ? i : i_lo);
         }
         T v[B];
-        if constexpr (MODE == 0) {  // map, I/Q/U: one packed-map gather per sample
-            typedef typename std::conditional<sizeof(T) == 4, float4, double4>::type T4;
-            typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type T2;
-            const int32_t* cb = a.cid + base;
-            const T2* wb = reinterpret_cast<const T2*>(a.w) + base;
-            const char* xpb = reinterpret_cast<const char*>(a.xp);
-            uint32_t cc[B];
-            T2 ww[B];
-#pragma unroll
-            for (int u = 0; u < B; ++u) cc[u] = (uint32_t)at_u32(cb, rr[u]);
-#pragma unroll
-            for (int u = 0; u < B; ++u) ww[u] = at_u32(wb, rr[u]);
-            T4 xx[B];  // byte offsets of the packed map fit 32 bits (n_obs < 2^27)
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                xx[u] = *reinterpret_cast<const T4*>(xpb + cc[u] * (uint32_t)sizeof(T4));
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                v[u] = ok[u] ? xx[u].x + ww[u].x * xx[u].y + ww[u].y * xx[u].z : (T)0;
-        } else if constexpr (MODE == 1) {  // I rows of the map (I-only plans, and IQU maps
+        if constexpr (MODE == 1) {  // I rows of the map (I-only plans, and IQU maps
                                            // whose Q and U rows are zero: the I weight is 1)
             const int32_t* cb = a.cid + base;
             int32_t cc[B];
