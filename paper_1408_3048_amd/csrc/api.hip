@@ -366,6 +366,8 @@ using clk = std::chrono::steady_clock;
 constexpr double kReplaceRatio = 1e-4;
 // iterations launched between two reads of the problem states
 constexpr int kChunk = 4;
+// values of residual histories copied to the host at a time (8 MB)
+constexpr size_t kHistCopy = (size_t)1 << 20;
 // samples from which launches issued one by one are as fast as replayed ones
 constexpr int64_t kGraphMaxSamples = int64_t(1) << 18;
 // Whether a plan's solves with preconditioner pc, on a stream of their own, replay graphs.  The two-level iterations (8
@@ -1125,23 +1127,28 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
     std::vector<int> status(B, MM_OK);
     std::vector<std::vector<double>> hist_all(B);
     auto wanted = [&](int i) { return inf[i].history && inf[i].history_cap > 0; };
-    // the recorded residuals of the problems that asked for them, in one copy
+    // the recorded residuals of the problems that asked for them, kHistCopy values a copy
     auto fetch_hist = [&](double scale) -> int {
         size_t len = 0;
         for (int i = 0; i < B; ++i)
             if (wanted(i)) len = std::max<size_t>(len, std::max(pl->h_sc[i].iter, 0));
         if (len == 0) return MM_OK;
-        std::vector<double> h(len * B);
-        // (a 2-D copy waits for the default stream as well)
-        if (B == 1)
-            MM_HIP(hipMemcpyAsync(h.data(), pl->hist.p, len * 8, hipMemcpyDeviceToHost, pl->stream));
-        else
-            MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, pl->hist.p, (size_t)pl->hstride * 8, len * 8,
-                                    B, hipMemcpyDeviceToHost, pl->stream));
-        MM_HIP(hipStreamSynchronize(pl->stream));
-        for (int i = 0; i < B; ++i)
-            for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)
-                hist_all[i].push_back(h[i * len + k] * scale);
+        const int group = (int)std::min<size_t>(B, std::max<size_t>(1, kHistCopy / len));
+        std::vector<double> h(len * group);
+        for (int b0 = 0; b0 < B; b0 += group) {
+            const int nb = std::min(group, B - b0);
+            const double* src = pl->hist.p + (size_t)b0 * pl->hstride;
+            // (a 2-D copy waits for the default stream as well)
+            if (nb == 1)
+                MM_HIP(hipMemcpyAsync(h.data(), src, len * 8, hipMemcpyDeviceToHost, pl->stream));
+            else
+                MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, src, (size_t)pl->hstride * 8, len * 8,
+                                        nb, hipMemcpyDeviceToHost, pl->stream));
+            MM_HIP(hipStreamSynchronize(pl->stream));
+            for (int i = b0; i < b0 + nb; ++i)
+                for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)
+                    hist_all[i].push_back(h[(i - b0) * len + k] * scale);
+        }
         return MM_OK;
     };
     if (precision == MM_FP64 || precision == MM_MIXED) {

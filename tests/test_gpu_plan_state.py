@@ -79,3 +79,29 @@ def test_ranges_of_the_coarse_build():
     none = Plan.from_scan(scans[0])
     assert none.az_pt_ranges().size == 0
     none.close()
+
+
+def test_histories_of_more_problems_than_one_copy_takes():
+    """700 problems of 64 samples, 1600 iterations each towards a tolerance out of reach: the
+    histories come in several copies, and each is its own problem's."""
+    B, n, it = 700, 64, 1600
+    r = np.random.default_rng(4)
+    pix = np.concatenate([b * 8 + r.permutation(np.arange(n) % 8) for b in range(B)])
+    off = np.arange(B * 2 + 1) * (n // 2)
+    psd = np.stack([r.uniform(0.5, 2, 2 * B), r.uniform(1, 2, 2 * B), np.ones(2 * B)], 1)
+    d = torch.from_numpy(r.standard_normal(B * n)).cuda()
+    kw = dict(n_stokes=1, lam=8, fft_len_f64=2048)
+    plan = Plan(torch.from_numpy(pix.astype(np.int32)).cuda(), None, 8 * B, off, psd,
+                problem_intervals=np.arange(B + 1) * 2, **kw)
+    _, info = plan.pcg_solve(plan.rhs(d), tol=1e-300, max_iter=it, raise_on_error=False)
+    per = info["problems"]
+    assert max(p["iterations"] for p in per) * B > 1 << 20
+    for b in (0, 1, 348, 654, 655, 656, 699):
+        one = Plan(torch.from_numpy((pix[b * n:(b + 1) * n] - 8 * b).astype(np.int32)).cuda(), None,
+                   8, np.array([0, n // 2, n]), psd[2 * b:2 * b + 2], **kw)
+        _, i1 = one.pcg_solve(one.rhs(d[b * n:(b + 1) * n].contiguous()), tol=1e-300, max_iter=it,
+                              raise_on_error=False)
+        assert per[b]["iterations"] == i1["iterations"]
+        assert np.array_equal(per[b]["history"], i1["history"]), b
+        one.close()
+    plan.close()
