@@ -1133,21 +1133,18 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
         for (int i = 0; i < B; ++i)
             if (wanted(i)) len = std::max<size_t>(len, std::max(pl->h_sc[i].iter, 0));
         if (len == 0) return MM_OK;
-        const int group = (int)std::min<size_t>(B, std::max<size_t>(1, kHistCopy / len));
-        std::vector<double> h(len * group);
+        // whole strides: a 2-D copy of the recorded parts waits for the default stream as well
+        const size_t hs = (size_t)pl->hstride;
+        const int group = (int)std::min<size_t>(B, std::max<size_t>(1, kHistCopy / hs));
+        std::vector<double> h((group - 1) * hs + len);
         for (int b0 = 0; b0 < B; b0 += group) {
             const int nb = std::min(group, B - b0);
-            const double* src = pl->hist.p + (size_t)b0 * pl->hstride;
-            // (a 2-D copy waits for the default stream as well)
-            if (nb == 1)
-                MM_HIP(hipMemcpyAsync(h.data(), src, len * 8, hipMemcpyDeviceToHost, pl->stream));
-            else
-                MM_HIP(hipMemcpy2DAsync(h.data(), len * 8, src, (size_t)pl->hstride * 8, len * 8,
-                                        nb, hipMemcpyDeviceToHost, pl->stream));
+            MM_HIP(hipMemcpyAsync(h.data(), pl->hist.p + b0 * hs, ((nb - 1) * hs + len) * 8,
+                                  hipMemcpyDeviceToHost, pl->stream));
             MM_HIP(hipStreamSynchronize(pl->stream));
             for (int i = b0; i < b0 + nb; ++i)
                 for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)
-                    hist_all[i].push_back(h[(i - b0) * len + k] * scale);
+                    hist_all[i].push_back(h[(i - b0) * hs + k] * scale);
         }
         return MM_OK;
     };

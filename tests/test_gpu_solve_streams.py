@@ -3,6 +3,7 @@
 import threading
 import time
 
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -16,18 +17,10 @@ from paper_1408_3048_amd import Plan  # noqa: E402
 from paper_1408_3048_amd._lib import MMError  # noqa: E402
 
 
-@pytest.mark.parametrize("history", [False, True])
-@pytest.mark.parametrize("coarse", [False, True])
-def test_solve_does_not_wait_for_later_work_on_the_callers_stream(coarse, history):
+def ends_before_later_work(plan, b, **kw):
     """While a thread solves on the default stream, another enqueues 2 s of work there: the
     solve, about half a second of iterations to a tolerance that it cannot meet, reads its
     states on a stream of its own and ends first."""
-    sc = synth.raster_iqu(side=16, spp=8, interval_len=512, seed_key=12, n_det=4, lam=64,
-                          fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
-    plan = Plan.from_scan(sc, coarse=coarse)
-    kw = dict(precond="2lvl" if coarse else "bj", tol=1e-30, history=history)
-    b = plan.rhs(torch.from_numpy(sc.noise).cuda())
-
     def solve(max_iter):
         t = time.perf_counter()
         try:
@@ -64,4 +57,27 @@ def test_solve_does_not_wait_for_later_work_on_the_callers_stream(coarse, histor
     end = time.perf_counter()
     th.join()
     assert done["at"] < end - 0.5, (done["s"], per_iter, max_iter)
+
+
+@pytest.mark.parametrize("history", [False, True])
+@pytest.mark.parametrize("coarse", [False, True])
+def test_solve_does_not_wait_for_later_work_on_the_callers_stream(coarse, history):
+    sc = synth.raster_iqu(side=16, spp=8, interval_len=512, seed_key=12, n_det=4, lam=64,
+                          fknee_range=(3.0, 6.0), alpha_range=(1.0, 2.0))
+    plan = Plan.from_scan(sc, coarse=coarse)
+    ends_before_later_work(plan, plan.rhs(torch.from_numpy(sc.noise).cuda()),
+                           precond="2lvl" if coarse else "bj", tol=1e-30, history=history)
+    plan.close()
+
+
+def test_histories_of_a_batch_do_not_wait_for_it():
+    r = np.random.default_rng(7)
+    n, n_pix, B = 4096, 64, 3
+    pix = np.concatenate([b * n_pix + r.permutation(np.arange(n) % n_pix) for b in range(B)])
+    off = np.arange(B * 4 + 1) * (n // 4)
+    psd = np.stack([r.uniform(0.5, 2, 4 * B), r.uniform(1, 2, 4 * B), np.ones(4 * B)], 1)
+    plan = Plan(torch.from_numpy(pix.astype(np.int32)).cuda(), None, n_pix * B, off, psd,
+                problem_intervals=np.arange(B + 1) * 4, n_stokes=1, lam=64)
+    ends_before_later_work(plan, plan.rhs(torch.from_numpy(r.standard_normal(B * n)).cuda()),
+                           precond="bj", tol=1e-30, history=True)
     plan.close()
