@@ -64,23 +64,23 @@ def fft_tile_flops(offsets, lam, n_r):
 TRAFFIC = {
     # 2^24-sample IQU raster, FP32 tile length 16384 (the autotuner's choice on it)
     "ninv32": dict(source="paper_1408_3048_amd/csrc/toeplitz.hip",
-                   sha256="cd2e953c88d19f7c5fe1fc16fff9055570537be31dddb0add467dcdef965c4b2",
-                   by_cfg={16384: dict(fetch_kib=138222.8, write_kib=65548.5)},
+                   sha256="cd0329c04b4056d7aeb6250c5831a37a3530f55fddf48e6d645d50e5c6b36c03",
+                   by_cfg={16384: dict(fetch_kib=138735.7, write_kib=65548.7)},
                    fetch_factor=2.0, write_factor=1.0),
     # P^T on the same scan, by work range (samples per wave)
     "pt32": dict(source="paper_1408_3048_amd/csrc/pointing.hip",
-                 sha256="68ae8d49cd97082a83cb652e06dc5fa913e4e846fb2dd2fa02a7d3455af8fbc1",
-                 by_cfg={512: dict(fetch_kib=135453.0, write_kib=6692.2)},
+                 sha256="00932a5a482ff4b6466cef3ed22ac4d9c1aaba3635062bd70edede8fe8e3af9b",
+                 by_cfg={512: dict(fetch_kib=135445.6, write_kib=6698.7)},
                  fetch_factor=2.0, write_factor=1.0),
     # one GPU's share of the ring scan (2^25 samples), FP32 tile length 16384
     "ring_ninv32": dict(source="paper_1408_3048_amd/csrc/toeplitz.hip",
-                        sha256="cd2e953c88d19f7c5fe1fc16fff9055570537be31dddb0add467dcdef965c4b2",
-                        by_cfg={16384: dict(fetch_kib=248375.1, write_kib=131072.0)},
+                        sha256="cd0329c04b4056d7aeb6250c5831a37a3530f55fddf48e6d645d50e5c6b36c03",
+                        by_cfg={16384: dict(fetch_kib=250540.4, write_kib=131072.0)},
                         fetch_factor=2.0, write_factor=1.0),
     "ring_pt32": dict(source="paper_1408_3048_amd/csrc/pointing.hip",
-                      sha256="68ae8d49cd97082a83cb652e06dc5fa913e4e846fb2dd2fa02a7d3455af8fbc1",
-                      by_cfg={512: dict(fetch_kib=290643.7, write_kib=41329.2),
-                              1024: dict(fetch_kib=294699.4, write_kib=43457.2)},
+                      sha256="00932a5a482ff4b6466cef3ed22ac4d9c1aaba3635062bd70edede8fe8e3af9b",
+                      by_cfg={512: dict(fetch_kib=290574.7, write_kib=41382.7),
+                              1024: dict(fetch_kib=295206.8, write_kib=43561.3)},
                       fetch_factor=2.0, write_factor=1.0),
 }
 
