@@ -147,8 +147,9 @@ __global__ void k_lag0_sum(const double* __restrict__ part, const int64_t* __res
 // of c(k), k <= B, where s = (-1)^f is the shift of block c + 1 by N/2.  Every block is
 // transformed once (u and v as one complex sequence u + i v, split by symmetry), a workgroup
 // takes kLfRun consecutive blocks (plus the one after them), keeping the spectra of the last
-// block and the running sum in registers (less a few that spill) for the frequency pairs (f, N - f), and writes its
-// sum; k_lag_inverse adds the sums of an interval in order and transforms back.
+// block and the running sum in registers (less a few that spill) for the frequency pairs
+// (f, N - f), and writes its sum; k_lag_inverse adds the sums of an interval in order and
+// transforms back.
 //
 // u and v can differ by many orders of magnitude (u = P mu against the residual v), and the
 // split of their common transform would carry the larger one's rounding into the other: each

@@ -370,9 +370,9 @@ constexpr int kChunk = 4;
 constexpr size_t kHistCopy = (size_t)1 << 20;
 // samples from which launches issued one by one are as fast as replayed ones
 constexpr int64_t kGraphMaxSamples = int64_t(1) << 18;
-// Whether a plan's solves with preconditioner pc, on a stream of their own, replay graphs.  The two-level iterations (8
-// launches and more) of small plans do: 21 iterations at 2^16 samples 1058 us against 1068,
-// with A-DEF2 1273 against 1304.  The 4 launches of a block-Jacobi iteration do not (2^14
+// Whether a plan's solves with preconditioner pc, on a stream of their own, replay graphs.  The
+// two-level iterations (8 launches and more) of small plans do: 21 iterations at 2^16 samples
+// 1058 us against 1068, with A-DEF2 1273 against 1304.  The 4 launches of a block-Jacobi iteration do not (2^14
 // samples 1049 against 995, 2^16 1060 against 1056), and from 2^18 samples on launches issued one
 // by one are as fast or faster (2^22 FP64 two-level 6470 replayed against 6350, 2^24 mixed
 // two-level 15820 against 15690, 48 problems of 150000 samples 6990 against 6790).

@@ -33,9 +33,10 @@ __device__ __forceinline__ void scan_step(T (&acc)[NV], bool take) {
 
 // Wave-level segmented reduction over pixel-sorted samples.
 //
-// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., at 32-bit
-// positions from a base sample (see mm_pos.h: the caller moves its pointers there), and walks them in chunks of 64*E samples aligned to E: lane l holds samples c + E l + e
-// (e < E), loaded with aligned vector loads so E gathers are in flight per lane.
+// A wave owns the sorted samples [i0, i1) of whole pixels p0, p0+1, ..., at 32-bit positions
+// from a base sample (see mm_pos.h: the caller moves its pointers there), and walks them in
+// chunks of 64*E samples aligned to E: lane l holds samples c + E l + e (e < E), loaded with
+// aligned vector loads so E gathers are in flight per lane.
 // Each lane first sums its own samples segment by segment, then one segmented
 // inclusive scan over the 64 lane summaries (flag: the lane holds a segment
 // start) gives every lane the partial sum entering it; the sample at a pixel's
