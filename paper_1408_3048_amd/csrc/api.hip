@@ -1133,18 +1133,18 @@ int mm_pcg_solve(mm_plan_t pl, const double* b, double* x, int pc, int precision
         for (int i = 0; i < B; ++i)
             if (wanted(i)) len = std::max<size_t>(len, std::max(pl->h_sc[i].iter, 0));
         if (len == 0) return MM_OK;
-        // whole strides: a 2-D copy of the recorded parts waits for the default stream as well
-        const size_t hs = (size_t)pl->hstride;
-        const int group = (int)std::min<size_t>(B, std::max<size_t>(1, kHistCopy / hs));
-        std::vector<double> h((group - 1) * hs + len);
-        for (int b0 = 0; b0 < B; b0 += group) {
-            const int nb = std::min(group, B - b0);
-            MM_HIP(hipMemcpyAsync(h.data(), pl->hist.p + b0 * hs, ((nb - 1) * hs + len) * 8,
+        // by iteration, so that the recorded part is one stretch (a 2-D copy of it waits for the
+        // default stream as well)
+        const size_t step = std::min(len, std::max<size_t>(1, kHistCopy / B));
+        std::vector<double> h(step * B);
+        for (size_t k0 = 0; k0 < len; k0 += step) {
+            const size_t k1 = std::min(len, k0 + step);
+            MM_HIP(hipMemcpyAsync(h.data(), pl->hist.p + k0 * B, (k1 - k0) * B * 8,
                                   hipMemcpyDeviceToHost, pl->stream));
             MM_HIP(hipStreamSynchronize(pl->stream));
-            for (int i = b0; i < b0 + nb; ++i)
-                for (int k = 0; wanted(i) && k < pl->h_sc[i].iter; ++k)
-                    hist_all[i].push_back(h[(i - b0) * hs + k] * scale);
+            for (int i = 0; i < B; ++i)
+                for (size_t k = k0; wanted(i) && k < k1 && (int)k < pl->h_sc[i].iter; ++k)
+                    hist_all[i].push_back(h[(k - k0) * B + i] * scale);
         }
         return MM_OK;
     };

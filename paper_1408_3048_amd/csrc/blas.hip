@@ -133,7 +133,7 @@ __device__ __forceinline__ int test_residual(const PcgCtl& c, int b, int initial
         s.iter = iter;
         s.rr = rr;
         s.rel = rel;
-        if (!initial && c.hist) c.hist[(int64_t)b * c.hstride + iter - 1] = rel;
+        if (!initial && c.hist) c.hist[(int64_t)(iter - 1) * c.B + b] = rel;
         if (st != kActive) {
             s.state = st;
             c.act[b] = 0;

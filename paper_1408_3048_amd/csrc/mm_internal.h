@@ -169,7 +169,7 @@ struct PcgCtl {
     const int* mask = nullptr;   // [B] problems that take part in this launch (nullptr: all)
     int* act = nullptr;          // [B] problems that iterate (cleared when a problem stops)
     double* rz_hist = nullptr;   // [B][hstride] r^T z after every iteration
-    double* hist = nullptr;      // [B][hstride] recursive relative residual, or nullptr
+    double* hist = nullptr;      // [hstride][B] recursive relative residual, or nullptr
     const int32_t* eblk = nullptr;
     const int32_t* pblk = nullptr;
     const int64_t* ooff = nullptr;
@@ -310,7 +310,7 @@ struct mm_plan_s {
     mm::DBuf<mm::PcgScalars> sc;        // [B]
     mm::PcgScalars* h_sc = nullptr;     // pinned host mirror [B]
     mm::DBuf<int> act, sel;             // [B] masks: iterating / in a residual evaluation
-    mm::DBuf<double> hist;              // residual history [B][hstride]
+    mm::DBuf<double> hist;              // residual history [hstride][B]
     mm::DBuf<double> rz_hist;           // r^T z per iteration [B][hstride]
     int hstride = 0;
     // Krylov recording of a solve (set only while mm_coarse_from_krylov runs)
