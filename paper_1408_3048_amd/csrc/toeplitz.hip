@@ -595,7 +595,9 @@ __global__ __launch_bounds__(NT, (tile_waves_per_simd<T, LOGM, NT>())) void k_to
 // and 67 / 50; 2^24 172 / 121 and 214 / 181; lambda = 512, 5.8e6 samples in ragged intervals
 // 49.0 / 35.6 and 64 / 53; 2^18 samples of one Stokes parameter, lambda = 1024 11.1 / 11.1 and
 // 13.2 / 11.4.  The map gather is what is left beside the transform: its loads and the
-// transforms of a CU's two workgroups overlap little.  The error against 64-bit FFTs of
+// transforms of a CU's two workgroups overlap little (counters at 2^24 samples, where the data
+// leave the last-level cache: 157 us, 712 MB for 470 that the samples need, 4.5 TB/s: there the
+// bytes of the halos bound it; vector issue 45%).  The error against 64-bit FFTs of
 // whole intervals fell from 1.0e-15 to 0.6e-15 (twiddle powers rounded once).
 //
 // The same kernel in FP32 (32 points per thread) gained nothing at 16384 points (raster of
